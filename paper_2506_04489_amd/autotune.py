@@ -20,7 +20,7 @@ import json
 import sys
 import time
 
-SIZES = [16, 24, 32, 48, 64, 96, 128, 192, 256, 384]
+SIZES = [16, 18, 24, 32, 36, 48, 54, 64, 72, 96, 108, 128, 144, 162, 192, 216, 256, 288, 324, 384]
 
 
 def main(argv=None) -> int:

@@ -62,6 +62,8 @@ template <int R> __device__ __forceinline__ void twiddle_powers(double2 *p) {
     if constexpr (R > 4) {
         p[4] = cmul64(p[2], p[2]);
         p[5] = cmul64(p[4], p[1]);
+    }
+    if constexpr (R > 6) {
         p[6] = cmul64(p[4], p[2]);
         p[7] = cmul64(p[4], p[3]);
     }
@@ -70,7 +72,7 @@ template <int R> __device__ __forceinline__ void twiddle_powers(double2 *p) {
 #pragma unroll
         for (int k = 1; k < R - 8; ++k) p[8 + k] = cmul64(p[8], p[k]);
     }
-    static_assert(R == 2 || R == 3 || R == 4 || R == 8 || R == 12 || R == 16, "radix");
+    static_assert(R == 2 || R == 3 || R == 4 || R == 6 || R == 8 || R == 12 || R == 16 || R == 18, "radix");
 }
 
 template <typename T> struct Twiddle {
@@ -277,6 +279,85 @@ template <bool INV, typename C> struct DFT<12, INV, C> {
     }
 };
 
+// length 6 as 2 x 3 with coprime factors (Good's mapping, no twiddles):
+// inputs (3 n1 + 2 n2) mod 6, outputs (3 k1 + 4 k2) mod 6
+template <bool INV, typename C> struct DFT<6, INV, C> {
+    __device__ __forceinline__ static void run(C *v) {
+        C a[3] = {v[0], v[2], v[4]}, b[3] = {v[3], v[5], v[1]};
+        DFT<3, INV, C>::run(a);
+        DFT<3, INV, C>::run(b);
+        v[0] = c_add(a[0], b[0]);
+        v[3] = c_sub(a[0], b[0]);
+        v[4] = c_add(a[1], b[1]);
+        v[1] = c_sub(a[1], b[1]);
+        v[2] = c_add(a[2], b[2]);
+        v[5] = c_sub(a[2], b[2]);
+    }
+};
+
+// v *= W9^E (forward W9 = exp(-2 pi i/9)) for the 3 x 3 split of length 9
+template <int E, bool INV, typename C> __device__ __forceinline__ C mul_w9(C a) {
+    using T = decltype(a.x);
+    T wr, wi;   // W9^E, forward
+    if constexpr (E == 1) {
+        wr = T(0.76604444311897803520239265055541668);    // cos(2 pi/9)
+        wi = T(-0.64278760968653932632264340990726343);   // -sin(2 pi/9)
+    } else if constexpr (E == 2) {
+        wr = T(0.17364817766693034885171662676931479);    // cos(4 pi/9)
+        wi = T(-0.98480775301220805936674302458952301);   // -sin(4 pi/9)
+    } else {
+        static_assert(E == 4, "exponent");
+        wr = T(-0.93969262078590838405410927732473147);   // cos(8 pi/9)
+        wi = T(-0.34202014332566873304409961468225959);   // -sin(8 pi/9)
+    }
+    if (INV) wi = -wi;
+    return C{fmadd(a.x, wr, -(a.y * wi)), fmadd(a.x, wi, a.y * wr)};
+}
+// length 9 as 3 x 3: X[k1 + 3 k2] = sum_n2 W3^(n2 k2) W9^(n2 k1)
+// sum_n1 W3^(n1 k1) x[3 n1 + n2]
+template <bool INV, typename C> struct DFT<9, INV, C> {
+    __device__ __forceinline__ static void run(C *v) {
+        C a[3][3];
+#pragma unroll
+        for (int n2 = 0; n2 < 3; ++n2) {
+#pragma unroll
+            for (int n1 = 0; n1 < 3; ++n1) a[n2][n1] = v[3 * n1 + n2];
+            DFT<3, INV, C>::run(a[n2]);            // a[n2][k1]
+        }
+        a[1][1] = mul_w9<1, INV>(a[1][1]);
+        a[1][2] = mul_w9<2, INV>(a[1][2]);
+        a[2][1] = mul_w9<2, INV>(a[2][1]);
+        a[2][2] = mul_w9<4, INV>(a[2][2]);
+#pragma unroll
+        for (int k1 = 0; k1 < 3; ++k1) {
+            C b[3] = {a[0][k1], a[1][k1], a[2][k1]};
+            DFT<3, INV, C>::run(b);                 // b[k2]
+#pragma unroll
+            for (int k2 = 0; k2 < 3; ++k2) v[k1 + 3 * k2] = b[k2];
+        }
+    }
+};
+
+// length 18 as 2 x 9 with coprime factors: inputs (9 n1 + 2 n2) mod 18,
+// outputs (9 k1 + 10 k2) mod 18
+template <bool INV, typename C> struct DFT<18, INV, C> {
+    __device__ __forceinline__ static void run(C *v) {
+        C a[9], b[9];
+#pragma unroll
+        for (int i = 0; i < 9; ++i) {
+            a[i] = v[2 * i];
+            b[i] = v[(9 + 2 * i) % 18];
+        }
+        DFT<9, INV, C>::run(a);
+        DFT<9, INV, C>::run(b);
+#pragma unroll
+        for (int k = 0; k < 9; ++k) {
+            v[(10 * k) % 18] = c_add(a[k], b[k]);
+            v[(9 + 10 * k) % 18] = c_sub(a[k], b[k]);
+        }
+    }
+};
+
 // ------------------------------------------------------------ radix plans
 // Forward radix sequence per padded length; variant PV = 0 is the default,
 // PV = 1 an alternative ordering or factorisation and PV = 2 a factorisation
@@ -303,18 +384,25 @@ PSP_PLAN(256, 0, 8, 8, 4)
 PSP_PLAN(384, 0, 8, 4, 4, 3)
 PSP_PLAN(512, 0, 8, 8, 8)
 PSP_PLAN(768, 0, 8, 8, 4, 3)
-// lengths 2^a 3^b with b >= 2: radix-3 stages (radix 12 where it saves a
-// stage and keeps every thread busy)
-PSP_PLAN(36, 0, 4, 3, 3)
-PSP_PLAN(72, 0, 8, 3, 3)
-PSP_PLAN(108, 0, 4, 3, 3, 3)
-PSP_PLAN(144, 0, 8, 2, 3, 3)
-PSP_PLAN(216, 0, 8, 3, 3, 3)
-PSP_PLAN(288, 0, 8, 4, 3, 3)
-PSP_PLAN(324, 0, 12, 3, 3, 3)
-PSP_PLAN(432, 0, 12, 12, 3)
+// lengths 2^a 3^b with b >= 2: two or three stages whose radices all divide
+// the values a thread holds (the largest radix), so that no thread idles in
+// a stage and a column crosses LDS once or twice per transform.  Chains of
+// radix-3 stages (144 = 8 2 3 3, 324 = 12 3 3 3, 648 = 8 3 3 3 3, ...)
+// crossed it up to four times with threads idle in most stages; with the
+// default tile the FP64 solve went from 202 to 144 us at n = 144 (2n =
+// 288 = 12 6 4), 80.6 to 68.4 us at n = 108 (6 6 6) and 2478 to 2297 us at
+// n = 324 (18 6 6), and with these lengths' tuned tiles to 139, 66 and 1878
+// (n = 216: 716 to 505, n = 288: 1430 to 1159).
+PSP_PLAN(36, 0, 6, 6)
+PSP_PLAN(72, 0, 12, 6)
+PSP_PLAN(108, 0, 6, 6, 3)
+PSP_PLAN(144, 0, 12, 12)
+PSP_PLAN(216, 0, 6, 6, 6)
+PSP_PLAN(288, 0, 12, 6, 4)
+PSP_PLAN(324, 0, 18, 18)
+PSP_PLAN(432, 0, 12, 6, 6)
 PSP_PLAN(576, 0, 12, 12, 4)
-PSP_PLAN(648, 0, 8, 3, 3, 3, 3)
+PSP_PLAN(648, 0, 18, 6, 6)
 // alternatives
 PSP_PLAN(128, 1, 4, 8, 4)
 PSP_PLAN(256, 1, 4, 8, 8)

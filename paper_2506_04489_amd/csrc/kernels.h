@@ -201,7 +201,7 @@ inline bool supported_length(int N) {
         default: return false;
     }
 }
-// lengths with a factor 9 (two or more radix-3 stages): instantiated in the
+// lengths with a factor 9 (radix 6, 12 and 18 stages): instantiated in the
 // passes_{f64,f32}_x*.hip files
 inline bool nine_length(int N) { return N % 9 == 0; }
 
