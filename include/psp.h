@@ -218,7 +218,7 @@ psp_status psp_plan_set_tuning(psp_plan *p, int k3_tiles, int i1_group);
  *            stores of the pass's output; passes 1..3 (along i2, i1, i2): 0: one
  *            128-byte row of k3 columns per workgroup (8 FP64 or 16 FP32
  *            columns), 1: half of one, 2: one row with the exchanges between
- *            FFT stages through half-size LDS buffers by position half,
+ *            FFT stages through half-size LDS buffers,
  *            3: one row with half the threads per column (two butterflies
  *            per thread and stage), 4: 2 and 3 together, 5: one row with the
  *            exchanges through half-size LDS buffers by column half, 6: 5 and

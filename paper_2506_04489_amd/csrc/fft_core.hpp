@@ -439,6 +439,10 @@ template <int N, int PV = 0> struct MaxRadix {
     }
 };
 
+template <int V> struct Const {
+    static constexpr int value = V;
+};
+
 // ---------------------------------------------------------------- engine
 // Column transform engine.  TPC threads per column; thread t owns butterflies
 // j = t + b*TPC (b < BPT(s)) of every stage.  LdsIdx maps (position, column)
@@ -564,14 +568,192 @@ template <typename T, int N, int TPC, bool INV, int PV = 0> struct Engine {
         }
     }
 
+    // component-wise exchange: COMP 0 moves the real parts, 1 the imaginary
+    // parts, through a buffer of N scalars per column
+    template <int s, int COMP, typename Idx>
+    __device__ __forceinline__ static void store_comp(const C *v, T *lds, int t, Idx idx) {
+        constexpr int r_ = R(s), nb = N / r_;
+#pragma unroll
+        for (int b = 0; b < BPT(s); ++b) {
+            const int j = t + b * TPC;
+            if ((nb % TPC == 0) || j < nb) {
+#pragma unroll
+                for (int r = 0; r < r_; ++r) lds[idx.scalar(out_pos<s>(j, r))] = COMP ? v[b * r_ + r].y : v[b * r_ + r].x;
+            }
+        }
+    }
+    template <int s, int COMP, typename Idx>
+    __device__ __forceinline__ static void load_comp(C *v, const T *lds, int t, Idx idx) {
+        constexpr int r_ = R(s), nb = N / r_;
+#pragma unroll
+        for (int b = 0; b < BPT(s); ++b) {
+            const int j = t + b * TPC;
+            if ((nb % TPC == 0) || j < nb) {
+#pragma unroll
+                for (int r = 0; r < r_; ++r) {
+                    const T x = lds[idx.scalar(in_pos<s>(j, r))];
+                    if (COMP) v[b * r_ + r].y = x;
+                    else v[b * r_ + r].x = x;
+                }
+            }
+        }
+    }
+
+    // ---- three-stage FP64 plans with 8 columns per workgroup: the exchange
+    // between the last two stages (forward; the first two, inverse) stays
+    // inside a wave.  Forward, with first, middle and last radix A, B, L: the
+    // middle butterfly j = a + A b (a < A, b < L) has outputs r at position
+    // a + A r + A B b, and the last butterfly a + A r takes those of all b.  A
+    // thread owns the middle butterflies of one b, and the threads of one a
+    // and every b are lanes of one wave (thread t = lane / 8 within it), so
+    // the exchange swaps bits of the register index with lane bits: 16 B of
+    // each value less through LDS each way, and no barrier.  What bounds the
+    // fused i1 pass beside its memory accesses is LDS: two exchanges and the
+    // twiddle reads per transform moved 180 bytes per value, now 116.  With
+    // the half-size exchanges by components (run_from) the pass went from
+    // 0.282 to 0.252 ms at n = 256 (plan 8 8 8, 62 registers, eight waves per
+    // SIMD), 0.534 to 0.462 at n = 288 and 1.185 to 1.166 at n = 384.  FP32
+    // is bound by its VALU work instead and keeps the LDS.  The inverse
+    // mirrors it (first butterfly a + A r, outputs b at (a + A r) L + b, to
+    // the middle butterfly a L + b).
+    static constexpr int LA = R(INV ? S - 1 : 0), LB = S == 3 ? R(1) : 1, LL = R(INV ? 0 : S - 1);
+    static constexpr bool LANES = S == 3 && sizeof(T) == 8 && (LL == 4 || LL == 8) && TPC % 8 == 0 &&
+                                  (N / (S == 3 ? LB : N)) % TPC == 0 && (N / LL) % TPC == 0;
+    static constexpr int LI = LANES ? N / LB / TPC : 1;      // middle butterflies per thread
+    static constexpr int LH = LANES ? N / LL / TPC : 1;      // last (inverse: first) butterflies per thread
+    __device__ __forceinline__ static int lane_b(int t) { return LL == 8 ? t % 8 : (t >> 1) & 3; }
+    __device__ __forceinline__ static int lane_a(int t, int i) {
+        const int u = LL == 8 ? t / 8 : (t & 1) | ((t >> 3) << 1);
+        return u + (TPC / LL) * i;
+    }
+    // index a + A r of the thread's h-th last (inverse: first) butterfly
+    __device__ __forceinline__ static int lane_end(int t, int h) {
+        const int f = h * LL + lane_b(t);
+        return lane_a(t, f / LB) + (f % LB) * LA;
+    }
+    __device__ __forceinline__ static void lane_swap(double &x, double &y, int bit) {
+        unsigned xl = (unsigned)__double2loint(x), xh = (unsigned)__double2hiint(x);
+        unsigned yl = (unsigned)__double2loint(y), yh = (unsigned)__double2hiint(y);
+        if (bit == 3) {          // row_ror:8, lanes 8-15 of x from y, 0-7 of y from x
+            const unsigned a = __builtin_amdgcn_update_dpp(xl, yl, 0x128, 0xf, 0xc, false);
+            const unsigned b = __builtin_amdgcn_update_dpp(xh, yh, 0x128, 0xf, 0xc, false);
+            yl = __builtin_amdgcn_update_dpp(yl, xl, 0x128, 0xf, 0x3, false);
+            yh = __builtin_amdgcn_update_dpp(yh, xh, 0x128, 0xf, 0x3, false);
+            xl = a;
+            xh = b;
+        } else if (bit == 4) {
+            const auto a = __builtin_amdgcn_permlane16_swap(xl, yl, false, false);
+            const auto b = __builtin_amdgcn_permlane16_swap(xh, yh, false, false);
+            xl = a[0], yl = a[1], xh = b[0], yh = b[1];
+        } else {
+            const auto a = __builtin_amdgcn_permlane32_swap(xl, yl, false, false);
+            const auto b = __builtin_amdgcn_permlane32_swap(xh, yh, false, false);
+            xl = a[0], yl = a[1], xh = b[0], yh = b[1];
+        }
+        x = __hiloint2double((int)xh, (int)xl);
+        y = __hiloint2double((int)yh, (int)yl);
+    }
+    // register l of each group of LL <-> lane b
+    __device__ __forceinline__ static void lane_exchange(C *v) {
+        constexpr int low = LL == 8 ? 3 : 4;       // lane bit of b's lowest bit
+#pragma unroll
+        for (int h = 0; h < LH; ++h)
+#pragma unroll
+            for (int m = 1, bit = low; m < LL; m *= 2, ++bit)
+#pragma unroll
+                for (int l = 0; l < LL; ++l)
+                    if (!(l & m)) {
+                        lane_swap(v[h * LL + l].x, v[h * LL + l + m].x, bit);
+                        lane_swap(v[h * LL + l].y, v[h * LL + l + m].y, bit);
+                    }
+    }
+    template <typename Idx, typename TW>
+    __device__ __forceinline__ static void run_lanes(C *v, C *lds, int t, Idx idx, const TW &tw) {
+        T *l = reinterpret_cast<T *>(lds);
+        if constexpr (!INV) {
+            compute<0>(v, t, tw);
+            // to the middle butterflies a + A b: by components, as in SPLIT
+            auto load = [&](auto comp) {
+#pragma unroll
+                for (int i = 0; i < LI; ++i)
+#pragma unroll
+                    for (int r = 0; r < LB; ++r) {
+                        const T x = l[idx.scalar(in_pos<1>(lane_a(t, i) + LA * lane_b(t), r))];
+                        if constexpr (decltype(comp)::value) v[i * LB + r].y = x;
+                        else v[i * LB + r].x = x;
+                    }
+            };
+            store_comp<0, 0>(v, l, t, idx);
+            __syncthreads();
+            load(Const<0>{});
+            __syncthreads();
+            store_comp<0, 1>(v, l, t, idx);
+            __syncthreads();
+            load(Const<1>{});
+            __syncthreads();
+#pragma unroll
+            for (int i = 0; i < LI; ++i) {
+                tw.template apply<LB, false>(v + i * LB, lane_a(t, i) * (N / (LA * LB)));
+                DFT<LB, false, C>::run(v + i * LB);
+            }
+            lane_exchange(v);
+#pragma unroll
+            for (int h = 0; h < LH; ++h) {
+                tw.template apply<LL, false>(v + h * LL, lane_end(t, h));
+                DFT<LL, false, C>::run(v + h * LL);
+            }
+        } else {
+#pragma unroll
+            for (int h = 0; h < LH; ++h) DFT<LL, true, C>::run(v + h * LL);
+            lane_exchange(v);
+#pragma unroll
+            for (int i = 0; i < LI; ++i) {
+                tw.template apply<LB, true>(v + i * LB, lane_b(t) * (N / (LL * LB)));
+                DFT<LB, true, C>::run(v + i * LB);
+            }
+            auto store = [&](auto comp) {
+#pragma unroll
+                for (int i = 0; i < LI; ++i)
+#pragma unroll
+                    for (int r = 0; r < LB; ++r)
+                        l[idx.scalar(out_pos<1>(lane_a(t, i) * LL + lane_b(t), r))] =
+                            decltype(comp)::value ? v[i * LB + r].y : v[i * LB + r].x;
+            };
+            store(Const<0>{});
+            __syncthreads();
+            load_comp<2, 0>(v, l, t, idx);
+            __syncthreads();
+            store(Const<1>{});
+            __syncthreads();
+            load_comp<2, 1>(v, l, t, idx);
+            __syncthreads();
+            compute<2>(v, t, tw);
+        }
+    }
+    // the last outputs (forward) or first inputs (inverse) of run_lanes: f(position, leg, value&)
+    template <typename F> __device__ __forceinline__ static void lane_ends(C *v, int t, F f) {
+#pragma unroll
+        for (int h = 0; h < LH; ++h) {
+            const int j = lane_end(t, h);
+#pragma unroll
+            for (int r = 0; r < LL; ++r) f(j + r * (N / LL), r, v[h * LL + r]);
+        }
+    }
+
     // stages [s, S) given stage-s inputs in registers; on return registers
     // hold the last stage's outputs at positions j + r N/R(S-1).  SPLIT: each
-    // exchange goes through an LDS buffer of N/2 positions in two phases.
+    // exchange goes through an LDS buffer of half the size in two phases.
+    // FP64: real parts, then imaginary parts; the new parts take the place of
+    // the old ones, so no value needs a staging register (H3 at n = 256, plan
+    // 16 8 4: 127 registers and four waves per SIMD instead of 150 and three,
+    // 0.277-0.284 -> 0.266 ms).  FP32: the lower half of the positions, then
+    // the upper; by components its 4-byte LDS accesses cost more than the
+    // staging registers (H2 at n = 384: 0.243 -> 0.316 ms).
     template <int s, bool SPLIT = false, typename Idx, typename TW>
     __device__ __forceinline__ static void run_from(C *v, C *lds, int t, Idx idx, const TW &tw) {
         compute<s>(v, t, tw);
         if constexpr (s + 1 < S) {
-            if constexpr (SPLIT) {
+            if constexpr (SPLIT && sizeof(T) == 4) {
                 // the phase-0 inputs of stage s+1 must not overwrite stage-s
                 // outputs still waiting for phase 1: stage them in lo[]
                 C lo[V];
@@ -584,6 +766,16 @@ template <typename T, int N, int TPC, bool INV, int PV = 0> struct Engine {
                 load_half<s + 1>(v, lds, t, idx, 1);
                 __syncthreads();
                 merge_lower<s + 1>(v, lo, t);
+            } else if constexpr (SPLIT) {
+                T *l = reinterpret_cast<T *>(lds);
+                store_comp<s, 0>(v, l, t, idx);
+                __syncthreads();
+                load_comp<s + 1, 0>(v, l, t, idx);
+                __syncthreads();
+                store_comp<s, 1>(v, l, t, idx);
+                __syncthreads();
+                load_comp<s + 1, 1>(v, l, t, idx);
+                __syncthreads();
             } else {
                 store_lds<s>(v, lds, t, idx);
                 __syncthreads();
@@ -621,6 +813,19 @@ template <typename T, int N, int TPC, bool INV, int PV = 0> struct Engine {
     template <typename F>
     __device__ __forceinline__ static void for_outputs(C *v, int t, F f) {
         constexpr int s = S - 1, r_ = R(s), nb = N / r_;
+#pragma unroll
+        for (int b = 0; b < BPT(s); ++b) {
+            const int j = t + b * TPC;
+            if ((nb % TPC == 0) || j < nb) {
+#pragma unroll
+                for (int r = 0; r < r_; ++r) f(j + r * nb, r, v[b * r_ + r]);
+            }
+        }
+    }
+    // the final outputs (forward) or first inputs (inverse): f(position, leg r, value&)
+    template <typename F>
+    __device__ __forceinline__ static void for_modes(C *v, int t, F f) {
+        constexpr int s = INV ? 0 : S - 1, r_ = R(s), nb = N / r_;
 #pragma unroll
         for (int b = 0; b < BPT(s); ++b) {
             const int j = t + b * TPC;

@@ -25,9 +25,10 @@ struct Job {
 //            3: 64 (one line per workgroup where a line takes 64 threads),
 //            4-7: 0-3 with nontemporal stores (H1 of X, H5 of u);
 //            H2-H4 (p = 1..3): 0: one 128-byte row tile of k3 columns per
-//            workgroup (8 FP64 / 16 FP32 columns), 1: half of one, 2: one
-//            tile with exchanges through half-size LDS buffers by position
-//            half, 3: one tile with half the threads per column (two
+//            workgroup (8 FP64 / 16 FP32 columns), 1: half of one (FP64:
+//            with exchanges as in 2), 2: one tile with exchanges through
+//            half-size LDS buffers (FP64 by components, FP32 by position
+//            half), 3: one tile with half the threads per column (two
 //            butterflies each), 4: 2 and 3, 5: one tile with exchanges
 //            through half-size LDS buffers by column half, 6: 5 and 3;
 //            also 7-13: 0-6 with nontemporal accesses (H2 its stores of A,

@@ -39,8 +39,10 @@ template <> struct LayoutTile<float> { static constexpr int W = 16; };
 
 // strided passes: W columns per workgroup, TPC threads per column.  XCH:
 // how values move between FFT stages: 0 through an LDS buffer of all N x W
-// positions; 1 in two phases by position half (half the LDS, a staging copy
-// in registers); 2 in two phases by column half (half the LDS, no staging).
+// positions; 1 in two phases through half the LDS, FP64 real parts before
+// imaginary parts (and one of a three-stage plan's two exchanges inside a
+// wave), FP32 by position half (a staging copy in registers); 2 in two
+// phases by column half (half the LDS, no staging).
 // HALF: half the threads per column, each with twice the butterflies of a
 // stage (fewer waves, more independent work per wave).
 template <typename T, int N, int PV, int W, int XCH_ = 0, bool HALF = false> struct StridedCfg {
@@ -56,18 +58,26 @@ template <typename T, int N, int PV, int W, int XCH_ = 0, bool HALF = false> str
 // line passes: Q complex lines per workgroup of about THR threads
 template <typename T, int N, int PV, int THR> struct LineCfg {
     static constexpr int TPC = N / MaxRadix<N, PV>::value();
-    static constexpr int Q = (THR / TPC) > 0 ? (THR / TPC) : 1;
-    static constexpr int THREADS = TPC * Q;
     static constexpr int LINE = N + N / 8;                          // padded line in LDS
+    static constexpr int QMAX = 144 * 1024 / (LINE * (int)sizeof(cplx<T>));   // lines that fit LDS
+    static constexpr int Q = THR / TPC < 1 ? 1 : THR / TPC < QMAX ? THR / TPC : QMAX;
+    static constexpr int THREADS = TPC * Q;
 };
 
 template <int W> struct IdxInter {   // (position, column) -> position*W + column
     int col;
     __device__ __forceinline__ int operator()(int pos) const { return pos * W + col; }
+    // one component of a value: the positions of an aligned group of four are
+    // permuted by the next bits, so that a stage's stores (positions a
+    // multiple of 8 apart) spread over the banks
+    __device__ __forceinline__ int scalar(int pos) const {
+        return ((pos & ~3) | ((pos ^ (pos >> 3)) & 3)) * W + col;
+    }
 };
 struct IdxLine {                     // column-major, one padding slot per 8 positions
     int base;
     __device__ __forceinline__ int operator()(int pos) const { return base + pos + (pos >> 3); }
+    __device__ __forceinline__ int scalar(int pos) const { return base + pos + (pos >> 3); }
 };
 
 // Plain accesses to the solve's buffers, all global memory, made through
@@ -182,10 +192,24 @@ __device__ __forceinline__ float2 scale_mode(float2 v, double m) {
     return float2{v.x * mf, v.y * mf};
 }
 
+// whether a strided pass with half-size exchange buffers keeps the exchange
+// of the last two (inverse: first two) stages inside a wave
+template <typename E, typename Cfg> constexpr bool lanes_on() { return Cfg::XCH == 1 && Cfg::SUB == 1 && E::LANES; }
+// final outputs of a forward, first inputs of an inverse strided transform
+template <typename E, typename Cfg, typename C, typename F>
+__device__ __forceinline__ void strided_modes(C *v, int t, F f) {
+    if constexpr (lanes_on<E, Cfg>())
+        E::lane_ends(v, t, f);
+    else
+        E::for_modes(v, t, f);
+}
+
 // the FFT stages of a strided pass with the configuration's exchange
 template <typename E, typename Cfg, int W, typename C, typename TW>
 __device__ __forceinline__ void strided_stages(C *v, C *lds, int t, int col, const TW &tw) {
-    if constexpr (Cfg::XCH == 2)
+    if constexpr (lanes_on<E, Cfg>())
+        E::run_lanes(v, lds, t, IdxInter<W>{col}, tw);
+    else if constexpr (Cfg::XCH == 2)
         E::template run_from_cols<0>(v, lds, t, IdxInter<W / 2>{col % (W / 2)}, tw, col < W / 2);
     else
         E::template run_from<0, Cfg::XCH == 1>(v, lds, t, IdxInter<W>{col}, tw);
@@ -328,7 +352,7 @@ k_y_fwd(JobRef jr, Chunk ck, int P, Twiddle<T> tw) {
         return c_zero<C>();
     });
     strided_stages<E, Cfg, W>(v, lds, t, col, twx);
-    E::for_outputs(v, t, [&](int pos, int, C &val) { a_store<CP>(&dst[(size_t)pos * ck.pa], val); });
+    strided_modes<E, Cfg>(v, t, [&](int pos, int, C &val) { a_store<CP>(&dst[(size_t)pos * ck.pa], val); });
 }
 
 // ------------------------------------------------------------------- H3
@@ -374,7 +398,7 @@ k_x_fused(JobRef jr, Chunk ck, int P, Twiddle<T> tw) {
     });
     const auto twx = tw_commit<T, N, Cfg::THREADS, true>(tw, twf, lds + Cfg::LDS_ELEMS);
     strided_stages<EF, Cfg, W>(v, lds, t, col, twx);
-    EF::for_outputs(v, t, [&](int pos, int r, C &val) {
+    strided_modes<EF, Cfg>(v, t, [&](int pos, int r, C &val) {
         // the mode's multiplier row |k1|: for an even last radix, legs below
         // R/2 hold the positions below n and the others those from n up
         constexpr int RL = EF::R(EF::S - 1);
@@ -416,16 +440,12 @@ k_y_inv(JobRef jr, Chunk ck, int P, Twiddle<T> tw) {
     C v[E::V];
     if constexpr (!FULL) {
         const C *src = (const C *)jb.A + a_index(ck, c, 0, i1);         // rows k2
-        E::for_inputs(v, t, [&](int pos, int) -> C {
-            if (valid) return a_load<CP>(&src[(size_t)pos * ck.pa]);
-            return c_zero<C>();
+        strided_modes<E, Cfg>(v, t, [&](int pos, int, C &val) {
+            val = valid ? a_load<CP>(&src[(size_t)pos * ck.pa]) : c_zero<C>();
         });
     } else {
         const C *src = (const C *)jb.A2 + (size_t)i1 * N * P + cg;
-        E::for_inputs(v, t, [&](int pos, int) -> C {
-            if (valid) return src[(size_t)pos * P];
-            return c_zero<C>();
-        });
+        strided_modes<E, Cfg>(v, t, [&](int pos, int, C &val) { val = valid ? src[(size_t)pos * P] : c_zero<C>(); });
     }
     strided_stages<E, Cfg, W>(v, lds, t, col, twx);
     constexpr int rows_out = FULL ? N : n;
@@ -530,10 +550,13 @@ template <int W_, int XC_, bool HF_> struct StridedTile {
     static constexpr int XC = XC_;
     static constexpr bool HF = HF_;
 };
+// half a row tile takes the half-size exchange in FP64: its workgroups are
+// what a size with few threads per column leaves too few of (n = 324: H3
+// 0.894 -> 0.787 ms)
 template <typename T, typename F> inline void with_cols(int tile, F &&f) {
     constexpr int LW = LayoutTile<T>::W;
     switch (tile) {
-        case 1: f(StridedTile<LW / 2, 0, false>{}); break;
+        case 1: f(StridedTile<LW / 2, sizeof(T) == 8 ? 1 : 0, false>{}); break;
         case 2: f(StridedTile<LW, 1, false>{}); break;
         case 3: f(StridedTile<LW, 0, true>{}); break;
         case 4: f(StridedTile<LW, 1, true>{}); break;
