@@ -530,10 +530,11 @@ psp_status psp_plan_get_multiplier(psp_plan *p, double *m_host) {
         std::vector<double> blk(bytes / 8);
         PSP_HIP(hipMemcpy(blk.data(), p->spec->mult, bytes, hipMemcpyDeviceToHost), "hipMemcpy(mult)");
         const size_t na = (size_t)d.n1 + 1, nb = (size_t)d.n2 + 1, nc = (size_t)d.n3 + 1;
+        const MultAt at{mult_rows(d.n1, d.n2, d.n3), P, d.n1 + 1};
         for (size_t a = 0; a < na; ++a)
             for (size_t b = 0; b < nb; ++b)
                 for (size_t c = 0; c < nc; ++c)
-                    m_host[(a * nb + b) * nc + c] = blk[((b * (P / 8) + c / 8) * na + a) * 8 + (c & 7)];
+                    m_host[(a * nb + b) * nc + c] = blk[at((int)a, (int)b, (int)c)];
         return PSP_OK;
     });
 }

@@ -370,10 +370,10 @@ template <int N, int PV> struct Plan;
         static constexpr int r[] = {__VA_ARGS__};                           \
         static constexpr int S = sizeof(r) / sizeof(int);                   \
     };
-PSP_PLAN(8, 0, 8)
-PSP_PLAN(12, 0, 4, 3)
+PSP_PLAN(8, 0, 4, 2)
+PSP_PLAN(12, 0, 6, 2)
 PSP_PLAN(16, 0, 4, 4)
-PSP_PLAN(24, 0, 8, 3)
+PSP_PLAN(24, 0, 6, 4)
 PSP_PLAN(32, 0, 8, 4)
 PSP_PLAN(48, 0, 4, 4, 3)
 PSP_PLAN(64, 0, 8, 8)
@@ -394,7 +394,7 @@ PSP_PLAN(768, 0, 8, 8, 4, 3)
 // n = 324 (18 6 6), and with these lengths' tuned tiles to 139, 66 and 1878
 // (n = 216: 716 to 505, n = 288: 1430 to 1159).
 PSP_PLAN(36, 0, 6, 6)
-PSP_PLAN(72, 0, 12, 6)
+PSP_PLAN(72, 0, 6, 12)
 PSP_PLAN(108, 0, 6, 6, 3)
 PSP_PLAN(144, 0, 12, 12)
 PSP_PLAN(216, 0, 6, 6, 6)

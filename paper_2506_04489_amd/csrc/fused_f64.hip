@@ -1,0 +1,22 @@
+// fused_f64.hip - the FP64 instantiation of the three-launch solve.
+#include "fused.hpp"
+
+namespace psp {
+
+#define PSP_FUSED(N) \
+    template hipError_t fused_solve<double, N>(const Job &, const Job *, int, const void *, hipStream_t);
+PSP_FUSED(8)
+PSP_FUSED(12)
+PSP_FUSED(16)
+PSP_FUSED(24)
+PSP_FUSED(32)
+PSP_FUSED(36)
+PSP_FUSED(48)
+PSP_FUSED(64)
+PSP_FUSED(72)
+PSP_FUSED(96)
+PSP_FUSED(108)
+PSP_FUSED(128)
+#undef PSP_FUSED
+
+}  // namespace psp

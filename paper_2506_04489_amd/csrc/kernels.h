@@ -84,6 +84,38 @@ constexpr bool r16_plan_exists(int N) { return N == 128 || N == 192 || N == 256 
 constexpr bool plan_exists(int N, int pv) {
     return pv == 0 || (pv == 1 && alt_plan_exists(N)) || (pv == 2 && r16_plan_exists(N));
 }
+// The three-launch solve of a cube (fused.hpp): the padded lengths it is
+// built for (all up to 128), and the radix plan of each axis it runs (0: i3,
+// 1: i2, 2: i1).  A solve takes it when its shape has these plans, so that
+// its result is bitwise that of the five passes.  Up to n = 64 a solve is
+// bound by launches and the latency of each kernel, which three launches
+// save (FP64, us: n = 32 20.7 -> 15.0, n = 64 26.9 -> 22.6).  Beyond, the
+// middle kernel's tile (n^2/4 FP64 values and their LDS exchanges) leaves one
+// or two workgroups per CU whose load, FFT and store phases do not overlap:
+// its 46 us at n = 96 and 44-59 us at n = 128 exceed what the two saved
+// passes over the i3 spectra give (whole solves 67 against 51, and 77 to 92
+// against 89 us).
+constexpr bool fused_length(int N) {
+    return N == 8 || N == 12 || N == 16 || N == 24 || N == 32 || N == 36 || N == 48 || N == 64 || N == 72 ||
+           N == 96 || N == 108 || N == 128;
+}
+constexpr int fused_plan(int N, int axis) { return N == 128 && axis == 2 ? 2 : 0; }
+inline bool fused_shape(int N, const Shape &s) {
+    return fused_length(N) && s.plan[0] == fused_plan(N, 0) && s.plan[4] == fused_plan(N, 0) &&
+           s.plan[1] == fused_plan(N, 1) && s.plan[3] == fused_plan(N, 1) && s.plan[2] == fused_plan(N, 2);
+}
+// Layout of a multiplier octant: element (|k1| = a, |k2| = b, k3 = c) of the
+// (n2+1) x P x (n1+1) doubles.  Rows ([b][c][a], for cubes of a fused
+// length): the fused pass reads all a of one (b, c).  Blocked
+// ([b][c/8][a][c%8], the others): the i1 pass reads 8 c of each a.
+struct MultAt {
+    bool rows;
+    int P, na;      // pitch of c, n1 + 1
+    __host__ __device__ size_t operator()(int a, int b, int c) const {
+        return rows ? ((size_t)b * P + c) * na + a : (((size_t)b * (P / 8) + c / 8) * na + a) * 8 + (c & 7);
+    }
+};
+__host__ __device__ inline bool mult_rows(int n1, int n2, int n3) { return n1 == n2 && n2 == n3 && fused_length(2 * n1); }
 inline bool shape_valid(int n, const Shape &s) {
     for (int p = 0; p < kPasses; ++p) {
         if (!plan_exists(2 * n, s.plan[p])) return false;

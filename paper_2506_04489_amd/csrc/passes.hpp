@@ -9,8 +9,8 @@
 //   A      : n planes of N rows of pa complex, [i1][k2][k3] after H2; H3
 //            updates it in place (pa = the k3 columns of one chunk, a
 //            multiple of the row tile; plane pitch a_plane(n, n, pa) >= N pa)
-//   mult   : (n+1)*P*(n+1) FP64, blocked [b][c/8][a][c%8] holding the
-//            multiplier m(|k1| = a, |k2| = b, k3 = c), zero for c > n
+//   mult   : (n+1)*P*(n+1) FP64 holding the multiplier m(|k1| = a, |k2| = b,
+//            k3 = c), zero for c > n, blocked or in rows (MultAt)
 // Passes (Algorithm 2):
 //   H1 k_z_r2c   : forward transform along i3 of the padded real lines, two
 //                  real lines per complex transform, n+1 bins kept
@@ -320,6 +320,7 @@ struct Chunk {
     int pa;         // k3 pitch of the chunk buffer A
     int n2;         // points along i2 (rows k2 of A: 2 n2)
     int n3;         // points along i3 (columns k3 <= n3 are valid)
+    int mrows;      // the multiplier is in rows (MultAt)
     long long plane;    // i1 pitch of A: a_plane(n1, n2, pa)
 };
 
@@ -390,7 +391,10 @@ k_x_fused(JobRef jr, Chunk ck, int P, Twiddle<T> tw) {
     const unsigned acol = (unsigned)(((size_t)k2 * ck.pa + c) * sizeof(C));   // rows i1
     const unsigned astep = (unsigned)((size_t)ck.plane * sizeof(C));
     const unsigned char *mbase = (const unsigned char *)jb.mult;
-    const unsigned mcol = (unsigned)((((size_t)(b * (P / 8) + cg / 8) * (n + 1)) * 8 + (cg & 7)) * sizeof(double));
+    // (only cubes of a fused length have the multiplier in rows)
+    const bool mrows = fused_length(N) && ck.mrows;
+    const unsigned mcol = (unsigned)(MultAt{mrows, P, n + 1}(0, b, cg) * sizeof(double));
+    const unsigned mstep = (mrows ? 1 : 8) * sizeof(double);
     C v[EF::V];
     EF::for_inputs(v, t, [&](int pos, int r) -> C {
         if (r < EF::R(0) / 2 && valid) return a_load<CP>((const C *)(abase + (acol + (unsigned)pos * astep)));
@@ -403,7 +407,7 @@ k_x_fused(JobRef jr, Chunk ck, int P, Twiddle<T> tw) {
         // R/2 hold the positions below n and the others those from n up
         constexpr int RL = EF::R(EF::S - 1);
         const int a = (RL % 2 == 0) ? (r < RL / 2 ? pos : N - pos) : (pos <= n ? pos : N - pos);
-        val = scale_mode(val, g_load((const double *)(mbase + (mcol + (unsigned)a * (8 * sizeof(double))))));
+        val = scale_mode(val, g_load((const double *)(mbase + (mcol + (unsigned)a * mstep))));
     });
     strided_stages<EI, Cfg, W>(v, lds, t, col, twx);
     if constexpr (!FULL) {
@@ -603,6 +607,10 @@ template <typename F> inline void with_threads(int tile, F &&f) {
     }
 }
 
+// the three-launch solve of a cube (fused.hpp, instantiated in fused_*.hip)
+template <typename T, int N> hipError_t fused_solve(const Job &one, const Job *table, int count, const void *tw64,
+                                                    hipStream_t st);
+
 // the five passes for `count` solves of one padded length: a single solve
 // (table == nullptr, pointers in `one`) or a table of `count` jobs.
 //   chunk_tiles > 0: H2-H4 over chunks of k3 row tiles (A holds one chunk);
@@ -632,13 +640,20 @@ hipError_t passes_impl(const Job &one, const Job *table, int count, int P, int c
     };
     const int ntile = ceil_div(dm.n3 + 1, LW);
     const int y = count;
+    const int mrows = mult_rows(dm.n1, dm.n2, dm.n3);
+    if constexpr (fused_length(N)) {
+        // per-pass events, partial passes and shrunk workspaces need the five
+        // passes; everything else of these lengths and plans runs fused
+        if (!full && !ev && mask == 0x1f && mrows && chunk_tiles <= 0 && i1_group <= 0 && fused_shape(N, sh))
+            return fused_solve<T, N>(one, table, count, tw64, st);
+    }
     if (full) {
         // uncropped variant (one chunk, default shape): A2 and Y2 (N x N x P,
         // row layout) receive all N outputs of the inverse transforms
         using SC = StridedCfg<T, N, 0, LW, 0, false>;
         using LC = LineCfg<T, N, 0, 256>;
         const JobRef jr{one, table};
-        const Chunk ck{0, ntile, ntile * LW, n, n, (long long)a_plane(n, n, ntile * LW, sizeof(cplx<T>))};
+        const Chunk ck{0, ntile, ntile * LW, n, n, mrows, (long long)a_plane(n, n, ntile * LW, sizeof(cplx<T>))};
         hipLaunchKernelGGL((k_z_r2c<T, N, 0, 256, 0>), dim3(ceil_div(n * n / 2, LC::Q), y), dim3(LC::THREADS), 0, st,
                            jr, n * n / 2, P, tw);
         hipLaunchKernelGGL((k_y_fwd<T, N, 0, LW, 0, false, 0>), dim3(n * ntile, y), dim3(SC::THREADS), 0, st, jr, ck, P, tw);
@@ -732,13 +747,13 @@ hipError_t passes_impl(const Job &one, const Job *table, int count, int P, int c
         }
         if (G < n1 && on(1)) {
             mark(1);
-            h2(jr, Chunk{0, ntile, PA, n2, n3, plane}, gs);
+            h2(jr, Chunk{0, ntile, PA, n2, n3, mrows, plane}, gs);
         }
     }
     const JobRef jr{one, table};
     for (int ch = 0; ch < nchunks; ++ch) {
         const int t0 = ch * ct, nt = std::min(ct, ntile - t0);
-        const Chunk ck{t0, nt, PA, n2, n3, plane};
+        const Chunk ck{t0, nt, PA, n2, n3, mrows, plane};
         if (G == n1 && on(1)) {
             mark(1);
             h2(jr, ck, n1);
@@ -763,7 +778,7 @@ hipError_t passes_impl(const Job &one, const Job *table, int count, int P, int c
         const JobRef jrg{j, table};
         if (G < n1 && on(3)) {
             mark(3);
-            h4(jrg, Chunk{0, ntile, PA, n2, n3, plane}, gs);
+            h4(jrg, Chunk{0, ntile, PA, n2, n3, mrows, plane}, gs);
         }
         if (on(4)) {
             mark(4);

@@ -137,7 +137,8 @@ __device__ __noinline__ void pb_x_fused(const PJob *jp, int item) {
     const int b = !valid ? 0 : (k2 <= n ? k2 : N - k2);
     const C *src = (const C *)jb.A + (size_t)k2 * jb.pa + c;      // rows i1
     const size_t step = (size_t)jb.plane;
-    const double *mrow = jb.mult + ((size_t)(b * (jb.P / 8) + c / 8) * (n + 1)) * 8 + (c & 7);
+    constexpr bool mrows = fused_length(N);         // every job here is a cube
+    const double *mrow = jb.mult + MultAt{mrows, jb.P, n + 1}(0, b, c);
     C v[EF::V];
     EF::for_inputs(v, t, [&](int pos, int r) -> C {
         if (r < EF::R(0) / 2 && valid) return g_load(&src[pos * step]);
@@ -146,7 +147,7 @@ __device__ __noinline__ void pb_x_fused(const PJob *jp, int item) {
     EF::template run_from<0>(v, lds, t, IdxInter<W>{col}, tw);
     EF::for_outputs(v, t, [&](int pos, int, C &val) {
         const int a = pos <= n ? pos : N - pos;
-        val = scale_mode(val, valid ? g_load(&mrow[(size_t)a * 8]) : 0.0);
+        val = scale_mode(val, valid ? g_load(&mrow[(size_t)a * (mrows ? 1 : 8)]) : 0.0);
     });
     EI::template run_from<0>(v, lds, t, IdxInter<W>{col}, tw);
     C *dst = (C *)jb.A + (size_t)k2 * jb.pa + c;

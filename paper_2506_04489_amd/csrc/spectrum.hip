@@ -77,7 +77,7 @@ k_spectrum(SpecTables tb, const double *__restrict__ omega, int R, int P, SpecSc
     const int rem = (int)(item % (na * ng));
     const int a0 = (rem / ng) * 16 * SPEC_AT, cgrp = (rem % ng) * SPEC_CT;
     const int row = lane & 15, kq = lane >> 4;
-    const int n1 = nA + 1;
+    const MultAt at{mult_rows(nA, nB, nC), P, nA + 1};
     const int abase = a0 + row, cbase = cgrp * 16 + row;
     v4d acc[SPEC_AT][SPEC_CT];
 #pragma unroll
@@ -114,7 +114,7 @@ k_spectrum(SpecTables tb, const double *__restrict__ omega, int R, int P, SpecSc
                 const int aa = a0 + t * 16 + kq + 4 * e;
                 if (aa <= nA && cc <= nC) {
                     const double k2 = sc.w[0] * ((double)aa * aa) + sc.w[1] * ((double)b * b) + sc.w[2] * ((double)cc * cc);
-                    mult[((size_t)(b * (P / 8) + cc / 8) * n1 + aa) * 8 + (cc & 7)] = sc.scale * k2 * acc[t][q][e];
+                    mult[at(aa, b, cc)] = sc.scale * k2 * acc[t][q][e];
                 }
             }
         }

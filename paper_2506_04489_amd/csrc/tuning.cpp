@@ -301,6 +301,37 @@ psp_status psp_autotune(psp_plan *p, int reps, void *stream, int *best_plan, int
                 }
             }
         }
+        // lengths with a three-launch solve: its plans, if it beats the five
+        // passes of the pick (events around the whole solve; per-pass events
+        // would make it run as five passes)
+        if (out == PSP_OK && fused_length(2 * n) && p->chunk_tiles <= 0 && p->i1_group <= 0) {
+            std::vector<size_t> fp = pick;
+            for (int i = 0; i < kPasses; ++i) {
+                const int pl = fused_plan(2 * n, i == 2 ? 2 : i == 0 || i == 4 ? 0 : 1);
+                size_t b = cand[i].size();
+                for (size_t c = 0; c < cand[i].size(); ++c)
+                    if (cand[i][c].first == pl && (b == cand[i].size() || best[i][c] < best[i][b])) b = c;
+                fp[i] = b;
+            }
+            float score = 0;
+            for (int in = 0; in < 2 && out == PSP_OK; ++in) {
+                SolveArgs a = solve_args(p, *w, in ? rho_b : rho, u);
+                a.shape = shape_of(fp);
+                std::vector<float> t;
+                for (int rep = 0; rep <= reps && out == PSP_OK; ++rep) {   // the first is a warm-up
+                    float ms = 0;
+                    if ((e = hipEventRecord(ev[0], st)) != hipSuccess || (e = launch_solve(a, st)) != hipSuccess ||
+                        (e = hipEventRecord(ev[1], st)) != hipSuccess || (e = hipEventSynchronize(ev[1])) != hipSuccess ||
+                        (e = hipEventElapsedTime(&ms, ev[0], ev[1])) != hipSuccess)
+                        out = hip_fail(e, "autotune solve");
+                    if (rep > 0) t.push_back(ms);
+                }
+                if (out != PSP_OK) break;
+                std::sort(t.begin(), t.end());
+                score += t[t.size() / 2];
+            }
+            if (out == PSP_OK && score < cur) pick = fp;
+        }
         if (out == PSP_OK && (e = hipStreamSynchronize(st)) != hipSuccess) out = hip_fail(e, "autotune");
         for (auto x : ev)
             if (x) (void)hipEventDestroy(x);
