@@ -291,10 +291,11 @@ psp_status psp_device_peaks(void *buf_a, void *buf_b, size_t bytes, void *stream
 void psp_plan_destroy(psp_plan *p);
 
 /* ---- captured solves (hipGraph) -------------------------------------------
- * psp_graph_capture records one solve of (plan, rho_dev, u_dev) as a HIP graph
- * with its own workspace; psp_graph_launch replays it on `stream` (one host
- * call for all passes).  psp_graph_capture_batched does the same for a
- * batch (as psp_solve_batched; the graph owns the workspaces and the device
+ * psp_graph_capture records one solve of (plan, rho_dev, u_dev) with its own
+ * workspace; psp_graph_launch replays it on `stream` (one host call for all
+ * passes, made as kernel launches: a HIP graph of so short a chain costs more
+ * host time).  psp_graph_capture_batched records a batch as a HIP graph
+ * (as psp_solve_batched; the graph owns the workspaces and the device
  * job table).  Replays of one graph must not overlap each other; the graph
  * keeps pointers to rho/u and to the plans' spectra, which must outlive it.
  * Capture synchronises `stream`. */

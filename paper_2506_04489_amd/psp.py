@@ -7,6 +7,7 @@ been built, importing works but the first call raises: there is no fallback.
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
 from typing import Optional, Sequence
 
@@ -99,6 +100,10 @@ def _check(status: int):
 def _stream_ptr(stream) -> Optional[int]:
     if stream is None:
         import torch
+        c = torch._C
+        if torch.cuda.is_initialized() and hasattr(c, "_cuda_getCurrentRawStream"):
+            # current_stream() without building a Stream object for each call
+            return c._cuda_getCurrentRawStream(c._cuda_getDevice())
         return torch.cuda.current_stream().cuda_stream
     if isinstance(stream, int):
         return stream
@@ -245,6 +250,10 @@ class Plan:
     def torch_dtype(self):
         return _torch_dtype(self.code)
 
+    @functools.cached_property
+    def _td(self):
+        return _torch_dtype(self.code)
+
     def close(self):
         if self._h:
             lib().psp_plan_destroy(self._h)
@@ -262,6 +271,8 @@ class Plan:
 
     def _check_tensor(self, t, shape):
         import torch
+        if type(t) is torch.Tensor and t.is_cuda and t.dtype is self._td and t.shape == shape and t.is_contiguous():
+            return
         if not isinstance(t, torch.Tensor) or not t.is_cuda:
             raise ValueError("expected a CUDA (HIP) tensor")
         if t.dtype != self.torch_dtype:
