@@ -26,6 +26,7 @@
 // consecutive columns of one row of every block.
 #pragma once
 #include "passes.hpp"
+#include "single.hpp"
 
 namespace psp {
 
@@ -72,12 +73,15 @@ template <int N, int PV, bool INV> struct SubSeq {
     }
 };
 
+// the largest padded length of the one-workgroup solve (single.hpp says why)
+constexpr int SINGLE_MAX = 16;
+
 // Tile of the fused kernels: J columns per workgroup of F1 and F3, KU bins
 // per thread and round of F3, NB blocks per workgroup of F2.
 template <typename T, int N> struct FusedCfg {
-    static constexpr int J = N == 36 || N == 12 || N == 8 ? 2 : N == 108 ? 6 : 4;
+    static constexpr int J = N == 36 ? 2 : N == 108 ? 6 : 4;
     static constexpr int KU = 3;
-    static constexpr int NB = N <= 16 ? 8 : N <= 32 ? 4 : N == 36 ? 2 : 1;
+    static constexpr int NB = N <= 32 ? 4 : N == 36 ? 2 : 1;
     // the 17 MB of A at n = 64 FP64 written and read past the caches: 26.7 ->
     // 24.2 us for the three launches; smaller ones lose 1 us by it
     static constexpr bool NT = N == 128 && sizeof(T) == 8;
@@ -429,21 +433,25 @@ k_f_inv(JobRef jr, Twiddle<T> tw) {
 // ------------------------------------------------------------ launch
 template <typename T, int N> hipError_t fused_solve(const Job &one, const Job *table, int count, const void *tw64,
                                                     hipStream_t st) {
-    using Cfg = FusedCfg<T, N>;
-    constexpr int n = N / 2, PZ = fused_plan(N, 0), PY = fused_plan(N, 1), PX = fused_plan(N, 2);
-    using G = FusedGeo<N, PY>;
-    using F1 = FusedLines<T, N, PZ, PY, Cfg::J>;
-    using F2 = FusedMid<T, N, PY, PX, Cfg::NB>;
-    static_assert((size_t)G::R * (n + 1) * G::template blk<T>() <=
-                      a_plane(n, n, (n / LayoutTile<T>::W + 1) * LayoutTile<T>::W, sizeof(cplx<T>)) * n,
-                  "the blocks fit the intermediate A");
     const Twiddle<T> tw = twiddle_of<T>(tw64);
     const JobRef jr{one, table};
-    const dim3 lines(xcd_blocks(n * F1::GROUPS), count);
-    hipLaunchKernelGGL((k_f_fwd<T, N, PZ, PY, Cfg::J, Cfg::NT ? 1 : 0>), lines, dim3(F1::THREADS), 0, st, jr, tw);
-    hipLaunchKernelGGL((k_f_mid<T, N, PY, PX, Cfg::NB, Cfg::NT ? 2 : 0>),
-                       dim3(xcd_blocks(ceil_div(F2::BLOCKS, Cfg::NB)), count), dim3(F2::THREADS), 0, st, jr, tw);
-    hipLaunchKernelGGL((k_f_inv<T, N, PZ, PY, Cfg::J, Cfg::KU, Cfg::NT ? 2 : 0>), lines, dim3(F1::THREADS), 0, st, jr, tw);
+    if constexpr (N <= SINGLE_MAX) {
+        hipLaunchKernelGGL((k_single<T, N>), dim3(1, count), dim3(SingleCfg<T, N>::THREADS), 0, st, jr, tw);
+    } else {
+        using Cfg = FusedCfg<T, N>;
+        constexpr int n = N / 2, PZ = fused_plan(N, 0), PY = fused_plan(N, 1), PX = fused_plan(N, 2);
+        using G = FusedGeo<N, PY>;
+        using F1 = FusedLines<T, N, PZ, PY, Cfg::J>;
+        using F2 = FusedMid<T, N, PY, PX, Cfg::NB>;
+        static_assert((size_t)G::R * (n + 1) * G::template blk<T>() <=
+                          a_plane(n, n, (n / LayoutTile<T>::W + 1) * LayoutTile<T>::W, sizeof(cplx<T>)) * n,
+                      "the blocks fit the intermediate A");
+        const dim3 lines(xcd_blocks(n * F1::GROUPS), count);
+        hipLaunchKernelGGL((k_f_fwd<T, N, PZ, PY, Cfg::J, Cfg::NT ? 1 : 0>), lines, dim3(F1::THREADS), 0, st, jr, tw);
+        hipLaunchKernelGGL((k_f_mid<T, N, PY, PX, Cfg::NB, Cfg::NT ? 2 : 0>),
+                           dim3(xcd_blocks(ceil_div(F2::BLOCKS, Cfg::NB)), count), dim3(F2::THREADS), 0, st, jr, tw);
+        hipLaunchKernelGGL((k_f_inv<T, N, PZ, PY, Cfg::J, Cfg::KU, Cfg::NT ? 2 : 0>), lines, dim3(F1::THREADS), 0, st, jr, tw);
+    }
     return hipGetLastError();
 }
 
