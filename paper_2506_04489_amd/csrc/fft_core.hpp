@@ -599,142 +599,165 @@ template <typename T, int N, int TPC, bool INV, int PV = 0> struct Engine {
         }
     }
 
-    // ---- three-stage FP64 plans with 8 columns per workgroup: the exchange
-    // between the last two stages (forward; the first two, inverse) stays
-    // inside a wave.  Forward, with first, middle and last radix A, B, L: the
-    // middle butterfly j = a + A b (a < A, b < L) has outputs r at position
-    // a + A r + A B b, and the last butterfly a + A r takes those of all b.  A
-    // thread owns the middle butterflies of one b, and the threads of one a
-    // and every b are lanes of one wave (thread t = lane / 8 within it), so
-    // the exchange swaps bits of the register index with lane bits: 16 B of
-    // each value less through LDS each way, and no barrier.  What bounds the
-    // fused i1 pass beside its memory accesses is LDS: two exchanges and the
-    // twiddle reads per transform moved 180 bytes per value, now 116.  With
-    // the half-size exchanges by components (run_from) the pass went from
-    // 0.282 to 0.252 ms at n = 256 (plan 8 8 8, 62 registers, eight waves per
-    // SIMD), 0.534 to 0.462 at n = 288 and 1.185 to 1.166 at n = 384.  FP32
-    // is bound by its VALU work instead and keeps the LDS.  The inverse
-    // mirrors it (first butterfly a + A r, outputs b at (a + A r) L + b, to
-    // the middle butterfly a L + b).
+    // ---- three-stage plans: the exchange between the last two stages
+    // (forward; the first two, inverse) stays inside a wave.  Forward, with
+    // first, middle and last radix A, B, L: the middle butterfly j = a + A b
+    // (a < A, b < L) has outputs r at position a + A r + A B b, and the last
+    // butterfly a + A r takes those of all b.  A thread owns the middle
+    // butterflies of one b, and the threads of one a and every b are lanes of
+    // one wave (a wave holds 64 / W consecutive threads t of each of W
+    // columns), so the exchange swaps bits of the register index with lane
+    // bits: 16 B (FP64) of each value less through LDS each way, and no
+    // barrier.  What bounds the fused i1 pass beside its memory accesses is
+    // LDS: two exchanges and the twiddle reads per transform moved 180 bytes
+    // per value, now 116.  With the half-size exchanges by components
+    // (run_from) the FP64 pass went from 0.282 to 0.252 ms at n = 256 (plan 8
+    // 8 8, 62 registers, eight waves per SIMD), 0.534 to 0.462 at n = 288 and
+    // 1.185 to 1.166 at n = 384.  The inverse mirrors it (first butterfly a +
+    // A r, outputs b at (a + A r) L + b, to the middle butterfly a L + b).
     static constexpr int LA = R(INV ? S - 1 : 0), LB = S == 3 ? R(1) : 1, LL = R(INV ? 0 : S - 1);
-    static constexpr bool LANES = S == 3 && sizeof(T) == 8 && (LL == 4 || LL == 8) && TPC % 8 == 0 &&
-                                  (N / (S == 3 ? LB : N)) % TPC == 0 && (N / LL) % TPC == 0;
-    static constexpr int LI = LANES ? N / LB / TPC : 1;      // middle butterflies per thread
-    static constexpr int LH = LANES ? N / LL / TPC : 1;      // last (inverse: first) butterflies per thread
-    __device__ __forceinline__ static int lane_b(int t) { return LL == 8 ? t % 8 : (t >> 1) & 3; }
-    __device__ __forceinline__ static int lane_a(int t, int i) {
-        const int u = LL == 8 ? t / 8 : (t & 1) | ((t >> 3) << 1);
+    static constexpr bool LFIT = S == 3 && (N / LB) % TPC == 0 && (N / LL) % TPC == 0;
+    template <int W> static constexpr bool lanes() {
+        return LFIT && ((W == 8 && (LL == 4 || LL == 8) && TPC % 8 == 0) || (W == 16 && LL == 4 && TPC % 4 == 0));
+    }
+    static constexpr int LI = LFIT ? N / LB / TPC : 1;      // middle butterflies per thread
+    static constexpr int LH = LFIT ? N / LL / TPC : 1;      // last (inverse: first) butterflies per thread
+    // b: the bits of t in lane bits 3..5 (W = 8, L = 8) or 4..5
+    template <int W> __device__ __forceinline__ static int lane_b(int t) {
+        return W == 16 ? t % 4 : LL == 8 ? t % 8 : (t >> 1) & 3;
+    }
+    template <int W> __device__ __forceinline__ static int lane_a(int t, int i) {
+        const int u = W == 16 ? t / 4 : LL == 8 ? t / 8 : (t & 1) | ((t >> 3) << 1);
         return u + (TPC / LL) * i;
     }
     // index a + A r of the thread's h-th last (inverse: first) butterfly
-    __device__ __forceinline__ static int lane_end(int t, int h) {
-        const int f = h * LL + lane_b(t);
-        return lane_a(t, f / LB) + (f % LB) * LA;
+    template <int W> __device__ __forceinline__ static int lane_end(int t, int h) {
+        const int f = h * LL + lane_b<W>(t);
+        return lane_a<W>(t, f / LB) + (f % LB) * LA;
     }
-    __device__ __forceinline__ static void lane_swap(double &x, double &y, int bit) {
+    // y of the lanes with bit 0 <-> x of the lanes with bit 1
+    template <int BIT> __device__ __forceinline__ static void lane_swap(unsigned &x, unsigned &y) {
+        if constexpr (BIT == 3) {          // row_ror:8 into lanes 8-15 of x, 0-7 of y
+            const unsigned a = __builtin_amdgcn_update_dpp(x, y, 0x128, 0xf, 0xc, false);
+            y = __builtin_amdgcn_update_dpp(y, x, 0x128, 0xf, 0x3, false);
+            x = a;
+        } else if constexpr (BIT == 4) {
+            const auto a = __builtin_amdgcn_permlane16_swap(x, y, false, false);
+            x = a[0], y = a[1];
+        } else {
+            const auto a = __builtin_amdgcn_permlane32_swap(x, y, false, false);
+            x = a[0], y = a[1];
+        }
+    }
+    template <int BIT> __device__ __forceinline__ static void lane_swap(double &x, double &y) {
         unsigned xl = (unsigned)__double2loint(x), xh = (unsigned)__double2hiint(x);
         unsigned yl = (unsigned)__double2loint(y), yh = (unsigned)__double2hiint(y);
-        if (bit == 3) {          // row_ror:8, lanes 8-15 of x from y, 0-7 of y from x
-            const unsigned a = __builtin_amdgcn_update_dpp(xl, yl, 0x128, 0xf, 0xc, false);
-            const unsigned b = __builtin_amdgcn_update_dpp(xh, yh, 0x128, 0xf, 0xc, false);
-            yl = __builtin_amdgcn_update_dpp(yl, xl, 0x128, 0xf, 0x3, false);
-            yh = __builtin_amdgcn_update_dpp(yh, xh, 0x128, 0xf, 0x3, false);
-            xl = a;
-            xh = b;
-        } else if (bit == 4) {
-            const auto a = __builtin_amdgcn_permlane16_swap(xl, yl, false, false);
-            const auto b = __builtin_amdgcn_permlane16_swap(xh, yh, false, false);
-            xl = a[0], yl = a[1], xh = b[0], yh = b[1];
-        } else {
-            const auto a = __builtin_amdgcn_permlane32_swap(xl, yl, false, false);
-            const auto b = __builtin_amdgcn_permlane32_swap(xh, yh, false, false);
-            xl = a[0], yl = a[1], xh = b[0], yh = b[1];
-        }
+        lane_swap<BIT>(xl, yl);
+        lane_swap<BIT>(xh, yh);
         x = __hiloint2double((int)xh, (int)xl);
         y = __hiloint2double((int)yh, (int)yl);
     }
-    // register l of each group of LL <-> lane b
-    __device__ __forceinline__ static void lane_exchange(C *v) {
-        constexpr int low = LL == 8 ? 3 : 4;       // lane bit of b's lowest bit
-#pragma unroll
-        for (int h = 0; h < LH; ++h)
-#pragma unroll
-            for (int m = 1, bit = low; m < LL; m *= 2, ++bit)
-#pragma unroll
-                for (int l = 0; l < LL; ++l)
-                    if (!(l & m)) {
-                        lane_swap(v[h * LL + l].x, v[h * LL + l + m].x, bit);
-                        lane_swap(v[h * LL + l].y, v[h * LL + l + m].y, bit);
-                    }
+    template <int BIT> __device__ __forceinline__ static void lane_swap(float &x, float &y) {
+        unsigned a = __float_as_uint(x), b = __float_as_uint(y);
+        lane_swap<BIT>(a, b);
+        x = __uint_as_float(a);
+        y = __uint_as_float(b);
     }
-    template <typename Idx, typename TW>
+    // register bit m of each group of LL <-> lane bit BIT, then the next
+    template <int BIT, int m> __device__ __forceinline__ static void lane_exchange(C *v) {
+#pragma unroll
+        for (int l = 0; l < LH * LL; ++l)
+            if (!(l & m)) {
+                lane_swap<BIT>(v[l].x, v[l + m].x);
+                lane_swap<BIT>(v[l].y, v[l + m].y);
+            }
+        if constexpr (2 * m < LL) lane_exchange<BIT + 1, 2 * m>(v);
+    }
+    template <int W, bool SPLIT, typename Idx, typename TW>
     __device__ __forceinline__ static void run_lanes(C *v, C *lds, int t, Idx idx, const TW &tw) {
+        constexpr int low = LL == 8 ? 3 : 4;       // lane bit of b's lowest bit
         T *l = reinterpret_cast<T *>(lds);
         if constexpr (!INV) {
             compute<0>(v, t, tw);
-            // to the middle butterflies a + A b: by components, as in SPLIT
-            auto load = [&](auto comp) {
+            // to the middle butterflies a + A b
+            auto load = [&](auto part) {
 #pragma unroll
                 for (int i = 0; i < LI; ++i)
 #pragma unroll
                     for (int r = 0; r < LB; ++r) {
-                        const T x = l[idx.scalar(in_pos<1>(lane_a(t, i) + LA * lane_b(t), r))];
-                        if constexpr (decltype(comp)::value) v[i * LB + r].y = x;
-                        else v[i * LB + r].x = x;
+                        const int pos = in_pos<1>(lane_a<W>(t, i) + LA * lane_b<W>(t), r);
+                        if constexpr (decltype(part)::value == 0) v[i * LB + r].x = l[idx.scalar(pos)];
+                        else if constexpr (decltype(part)::value == 1) v[i * LB + r].y = l[idx.scalar(pos)];
+                        else v[i * LB + r] = lds[idx(pos)];
                     }
             };
-            store_comp<0, 0>(v, l, t, idx);
-            __syncthreads();
-            load(Const<0>{});
-            __syncthreads();
-            store_comp<0, 1>(v, l, t, idx);
-            __syncthreads();
-            load(Const<1>{});
+            if constexpr (SPLIT) {
+                store_comp<0, 0>(v, l, t, idx);
+                __syncthreads();
+                load(Const<0>{});
+                __syncthreads();
+                store_comp<0, 1>(v, l, t, idx);
+                __syncthreads();
+                load(Const<1>{});
+            } else {
+                store_lds<0>(v, lds, t, idx);
+                __syncthreads();
+                load(Const<2>{});
+            }
             __syncthreads();
 #pragma unroll
             for (int i = 0; i < LI; ++i) {
-                tw.template apply<LB, false>(v + i * LB, lane_a(t, i) * (N / (LA * LB)));
+                tw.template apply<LB, false>(v + i * LB, lane_a<W>(t, i) * (N / (LA * LB)));
                 DFT<LB, false, C>::run(v + i * LB);
             }
-            lane_exchange(v);
+            lane_exchange<low, 1>(v);
 #pragma unroll
             for (int h = 0; h < LH; ++h) {
-                tw.template apply<LL, false>(v + h * LL, lane_end(t, h));
+                tw.template apply<LL, false>(v + h * LL, lane_end<W>(t, h));
                 DFT<LL, false, C>::run(v + h * LL);
             }
         } else {
 #pragma unroll
             for (int h = 0; h < LH; ++h) DFT<LL, true, C>::run(v + h * LL);
-            lane_exchange(v);
+            lane_exchange<low, 1>(v);
 #pragma unroll
             for (int i = 0; i < LI; ++i) {
-                tw.template apply<LB, true>(v + i * LB, lane_b(t) * (N / (LL * LB)));
+                tw.template apply<LB, true>(v + i * LB, lane_b<W>(t) * (N / (LL * LB)));
                 DFT<LB, true, C>::run(v + i * LB);
             }
-            auto store = [&](auto comp) {
+            auto store = [&](auto part) {
 #pragma unroll
                 for (int i = 0; i < LI; ++i)
 #pragma unroll
-                    for (int r = 0; r < LB; ++r)
-                        l[idx.scalar(out_pos<1>(lane_a(t, i) * LL + lane_b(t), r))] =
-                            decltype(comp)::value ? v[i * LB + r].y : v[i * LB + r].x;
+                    for (int r = 0; r < LB; ++r) {
+                        const int pos = out_pos<1>(lane_a<W>(t, i) * LL + lane_b<W>(t), r);
+                        if constexpr (decltype(part)::value == 0) l[idx.scalar(pos)] = v[i * LB + r].x;
+                        else if constexpr (decltype(part)::value == 1) l[idx.scalar(pos)] = v[i * LB + r].y;
+                        else lds[idx(pos)] = v[i * LB + r];
+                    }
             };
-            store(Const<0>{});
-            __syncthreads();
-            load_comp<2, 0>(v, l, t, idx);
-            __syncthreads();
-            store(Const<1>{});
-            __syncthreads();
-            load_comp<2, 1>(v, l, t, idx);
+            if constexpr (SPLIT) {
+                store(Const<0>{});
+                __syncthreads();
+                load_comp<2, 0>(v, l, t, idx);
+                __syncthreads();
+                store(Const<1>{});
+                __syncthreads();
+                load_comp<2, 1>(v, l, t, idx);
+            } else {
+                store(Const<2>{});
+                __syncthreads();
+                load_lds<2>(v, lds, t, idx);
+            }
             __syncthreads();
             compute<2>(v, t, tw);
         }
     }
     // the last outputs (forward) or first inputs (inverse) of run_lanes: f(position, leg, value&)
-    template <typename F> __device__ __forceinline__ static void lane_ends(C *v, int t, F f) {
+    template <int W, typename F> __device__ __forceinline__ static void lane_ends(C *v, int t, F f) {
 #pragma unroll
         for (int h = 0; h < LH; ++h) {
-            const int j = lane_end(t, h);
+            const int j = lane_end<W>(t, h);
 #pragma unroll
             for (int r = 0; r < LL; ++r) f(j + r * (N / LL), r, v[h * LL + r]);
         }

@@ -53,6 +53,7 @@ template <typename T, int N, int PV, int W, int XCH_ = 0, bool HALF = false> str
     static constexpr int XCH = XCH_;
     static constexpr int LDS_ELEMS = XCH ? N * W / 2 : N * W;
     static constexpr int SUB = LayoutTile<T>::W / W;     // workgroups per row tile
+    static constexpr int COLS = W;
 };
 
 // line passes: Q complex lines per workgroup of about THR threads
@@ -192,14 +193,16 @@ __device__ __forceinline__ float2 scale_mode(float2 v, double m) {
     return float2{v.x * mf, v.y * mf};
 }
 
-// whether a strided pass with half-size exchange buffers keeps the exchange
-// of the last two (inverse: first two) stages inside a wave
-template <typename E, typename Cfg> constexpr bool lanes_on() { return Cfg::XCH == 1 && Cfg::SUB == 1 && E::LANES; }
+// whether a strided pass keeps the exchange of the last two (inverse: first
+// two) stages inside a wave
+template <typename T, typename E, typename Cfg> constexpr bool lanes_on() {
+    return (Cfg::XCH == 0 || (Cfg::XCH == 1 && sizeof(T) == 8)) && E::template lanes<Cfg::COLS>();
+}
 // final outputs of a forward, first inputs of an inverse strided transform
 template <typename E, typename Cfg, typename C, typename F>
 __device__ __forceinline__ void strided_modes(C *v, int t, F f) {
-    if constexpr (lanes_on<E, Cfg>())
-        E::lane_ends(v, t, f);
+    if constexpr (lanes_on<decltype(v->x), E, Cfg>())
+        E::template lane_ends<Cfg::COLS>(v, t, f);
     else
         E::for_modes(v, t, f);
 }
@@ -207,8 +210,8 @@ __device__ __forceinline__ void strided_modes(C *v, int t, F f) {
 // the FFT stages of a strided pass with the configuration's exchange
 template <typename E, typename Cfg, int W, typename C, typename TW>
 __device__ __forceinline__ void strided_stages(C *v, C *lds, int t, int col, const TW &tw) {
-    if constexpr (lanes_on<E, Cfg>())
-        E::run_lanes(v, lds, t, IdxInter<W>{col}, tw);
+    if constexpr (lanes_on<decltype(v->x), E, Cfg>())
+        E::template run_lanes<W, Cfg::XCH == 1>(v, lds, t, IdxInter<W>{col}, tw);
     else if constexpr (Cfg::XCH == 2)
         E::template run_from_cols<0>(v, lds, t, IdxInter<W / 2>{col % (W / 2)}, tw, col < W / 2);
     else
