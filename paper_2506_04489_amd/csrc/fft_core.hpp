@@ -439,6 +439,49 @@ template <int N, int PV = 0> struct MaxRadix {
     }
 };
 
+// ------------------------------------------------- register <-> lane bits
+// y of the lanes with bit 0 <-> x of the lanes with bit 1 of lane bit BIT
+template <int BIT> __device__ __forceinline__ void lane_swap(unsigned &x, unsigned &y) {
+    if constexpr (BIT == 3) {          // row_ror:8 into lanes 8-15 of x, 0-7 of y
+        const unsigned a = __builtin_amdgcn_update_dpp(x, y, 0x128, 0xf, 0xc, false);
+        y = __builtin_amdgcn_update_dpp(y, x, 0x128, 0xf, 0x3, false);
+        x = a;
+    } else if constexpr (BIT == 4) {
+        const auto a = __builtin_amdgcn_permlane16_swap(x, y, false, false);
+        x = a[0], y = a[1];
+    } else {
+        static_assert(BIT == 5, "lane bit");
+        const auto a = __builtin_amdgcn_permlane32_swap(x, y, false, false);
+        x = a[0], y = a[1];
+    }
+}
+template <int BIT> __device__ __forceinline__ void lane_swap(double &x, double &y) {
+    unsigned xl = (unsigned)__double2loint(x), xh = (unsigned)__double2hiint(x);
+    unsigned yl = (unsigned)__double2loint(y), yh = (unsigned)__double2hiint(y);
+    lane_swap<BIT>(xl, yl);
+    lane_swap<BIT>(xh, yh);
+    x = __hiloint2double((int)xh, (int)xl);
+    y = __hiloint2double((int)yh, (int)yl);
+}
+template <int BIT> __device__ __forceinline__ void lane_swap(float &x, float &y) {
+    unsigned a = __float_as_uint(x), b = __float_as_uint(y);
+    lane_swap<BIT>(a, b);
+    x = __uint_as_float(a);
+    y = __uint_as_float(b);
+}
+// in each group of L of COUNT values: the bits of the index within the group
+// <-> the lane bits from BIT up (to bit 5 for the highest)
+template <int L, int COUNT, int BIT = (L == 8 ? 3 : 4), int m = 1, typename C>
+__device__ __forceinline__ void lane_exchange(C *v) {
+#pragma unroll
+    for (int l = 0; l < COUNT; ++l)
+        if (!(l & m)) {
+            lane_swap<BIT>(v[l].x, v[l + m].x);
+            lane_swap<BIT>(v[l].y, v[l + m].y);
+        }
+    if constexpr (2 * m < L) lane_exchange<L, COUNT, BIT + 1, 2 * m>(v);
+}
+
 template <int V> struct Const {
     static constexpr int value = V;
 };
@@ -635,47 +678,8 @@ template <typename T, int N, int TPC, bool INV, int PV = 0> struct Engine {
         const int f = h * LL + lane_b<W>(t);
         return lane_a<W>(t, f / LB) + (f % LB) * LA;
     }
-    // y of the lanes with bit 0 <-> x of the lanes with bit 1
-    template <int BIT> __device__ __forceinline__ static void lane_swap(unsigned &x, unsigned &y) {
-        if constexpr (BIT == 3) {          // row_ror:8 into lanes 8-15 of x, 0-7 of y
-            const unsigned a = __builtin_amdgcn_update_dpp(x, y, 0x128, 0xf, 0xc, false);
-            y = __builtin_amdgcn_update_dpp(y, x, 0x128, 0xf, 0x3, false);
-            x = a;
-        } else if constexpr (BIT == 4) {
-            const auto a = __builtin_amdgcn_permlane16_swap(x, y, false, false);
-            x = a[0], y = a[1];
-        } else {
-            const auto a = __builtin_amdgcn_permlane32_swap(x, y, false, false);
-            x = a[0], y = a[1];
-        }
-    }
-    template <int BIT> __device__ __forceinline__ static void lane_swap(double &x, double &y) {
-        unsigned xl = (unsigned)__double2loint(x), xh = (unsigned)__double2hiint(x);
-        unsigned yl = (unsigned)__double2loint(y), yh = (unsigned)__double2hiint(y);
-        lane_swap<BIT>(xl, yl);
-        lane_swap<BIT>(xh, yh);
-        x = __hiloint2double((int)xh, (int)xl);
-        y = __hiloint2double((int)yh, (int)yl);
-    }
-    template <int BIT> __device__ __forceinline__ static void lane_swap(float &x, float &y) {
-        unsigned a = __float_as_uint(x), b = __float_as_uint(y);
-        lane_swap<BIT>(a, b);
-        x = __uint_as_float(a);
-        y = __uint_as_float(b);
-    }
-    // register bit m of each group of LL <-> lane bit BIT, then the next
-    template <int BIT, int m> __device__ __forceinline__ static void lane_exchange(C *v) {
-#pragma unroll
-        for (int l = 0; l < LH * LL; ++l)
-            if (!(l & m)) {
-                lane_swap<BIT>(v[l].x, v[l + m].x);
-                lane_swap<BIT>(v[l].y, v[l + m].y);
-            }
-        if constexpr (2 * m < LL) lane_exchange<BIT + 1, 2 * m>(v);
-    }
     template <int W, bool SPLIT, typename Idx, typename TW>
     __device__ __forceinline__ static void run_lanes(C *v, C *lds, int t, Idx idx, const TW &tw) {
-        constexpr int low = LL == 8 ? 3 : 4;       // lane bit of b's lowest bit
         T *l = reinterpret_cast<T *>(lds);
         if constexpr (!INV) {
             compute<0>(v, t, tw);
@@ -710,7 +714,7 @@ template <typename T, int N, int TPC, bool INV, int PV = 0> struct Engine {
                 tw.template apply<LB, false>(v + i * LB, lane_a<W>(t, i) * (N / (LA * LB)));
                 DFT<LB, false, C>::run(v + i * LB);
             }
-            lane_exchange<low, 1>(v);
+            lane_exchange<LL, LH * LL>(v);
 #pragma unroll
             for (int h = 0; h < LH; ++h) {
                 tw.template apply<LL, false>(v + h * LL, lane_end<W>(t, h));
@@ -719,7 +723,7 @@ template <typename T, int N, int TPC, bool INV, int PV = 0> struct Engine {
         } else {
 #pragma unroll
             for (int h = 0; h < LH; ++h) DFT<LL, true, C>::run(v + h * LL);
-            lane_exchange<low, 1>(v);
+            lane_exchange<LL, LH * LL>(v);
 #pragma unroll
             for (int i = 0; i < LI; ++i) {
                 tw.template apply<LB, true>(v + i * LB, lane_b<W>(t) * (N / (LL * LB)));

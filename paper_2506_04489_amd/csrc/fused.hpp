@@ -19,7 +19,10 @@
 // theirs.  These sizes are bound by launches (three empty ones in a row take
 // 7.5 us) and by the chain of latencies inside each kernel; solves went from
 // five launches to, FP64 us per solve, 15.0 (from 20.7) at n = 16 and 32,
-// 21.0 (24.8) at n = 48, 22.6 (26.9) at n = 64; FP32 18.8 (23.5) at n = 64.
+// 21.0 (24.8) at n = 48, 22.6 (26.9) at n = 64, 77.9 (89.4) at n = 128; FP32
+// 18.8 (23.5) at n = 64, 50.5 (56.0) at n = 128.  Large ones are bound by F2
+// (42 of 75 us at n = 128), whose exchanges go through LDS; k_f_midw, which
+// does two of six in registers, took it from 59 us.
 //
 // A holds R (n + 1) blocks [r][k3] of n rows i1 of M columns j (block pitch
 // FusedGeo::BLK): F2 reads and writes whole blocks, F1 and F3 touch J
@@ -79,12 +82,15 @@ constexpr int SINGLE_MAX = 16;
 // Tile of the fused kernels: J columns per workgroup of F1 and F3, KU bins
 // per thread and round of F3, NB blocks per workgroup of F2.
 template <typename T, int N> struct FusedCfg {
-    static constexpr int J = N == 36 ? 2 : N == 108 ? 6 : 4;
-    static constexpr int KU = 3;
+    static constexpr int J = N == 36 ? 2 : N == 108 ? 6 : N == 256 ? 8 : 4;
+    static constexpr int KU = N == 256 ? 1 : N == 144 ? 2 : 3;
     static constexpr int NB = N <= 32 ? 4 : N == 36 ? 2 : 1;
-    // the 17 MB of A at n = 64 FP64 written and read past the caches: 26.7 ->
-    // 24.2 us for the three launches; smaller ones lose 1 us by it
+    // the 17 MB of A of one solve at n = 64 FP64 written and read past the
+    // caches: 26.7 -> 24.2 us for the three launches (other sizes and several
+    // solves in one launch lose by it, n = 128 74 -> 84 us)
     static constexpr bool NT = N == 128 && sizeof(T) == 8;
+    // whether the plans fit k_f_midw
+    static constexpr bool W = N == 128 || N == 256;
 };
 
 // consecutive work items on one XCD (workgroups go to the 8 XCDs in turn):
@@ -353,6 +359,145 @@ k_f_mid(JobRef jr, Twiddle<T> tw) {
     }
 }
 
+// F2 for i2 plans {R, A, 4} and i1 plans {16, B}, one block per workgroup.
+// The threads of the radix-4 M-point stage and of the i1 transform's first
+// stage are matched so that the data pass between them in registers: thread
+// (t, h, c) does the radix-4 butterflies c of the rows t + (h + 4 e) N/16 (e =
+// 0, 1), whose outputs are the columns c + A q, and then transforms column c
+// + A h, whose first-stage legs are the rows t + l N/16 of all four h.  With h
+// in lane bits 4 and 5 that is a swap of register with lane bits.  The
+// threads t of a column are lanes of one wave, so the i1 exchange needs no
+// workgroup barrier.  k_f_mid moved every value through LDS six times between
+// twelve barriers, this moves it four times between five.
+template <typename T, int N, int PY, int PX> struct FusedMidW {
+    using G = FusedGeo<N, PY>;
+    static constexpr int TPC = N / 16, A4 = G::M / 4, THREADS = G::M * TPC;
+    static constexpr int ELINE = N + N / 8 + 1;                 // column of the i1 exchange: scalars in FP64, values in FP32
+    static constexpr int MLINE = (N / 2 * 9 / 8) | 1;           // column of the M-point exchange, values
+    static constexpr int ES = G::M * ELINE / (sizeof(T) == 8 ? 2 : 1) + 1;
+    static constexpr int ELEMS = ES > G::M * MLINE ? ES : G::M * MLINE;
+    static constexpr int BLOCKS = G::R * (N / 2 + 1);
+    static_assert(Plan<N, PY>::S == 3 && Plan<N, PY>::r[2] == 4 && Plan<N, PX>::S == 2 && Plan<N, PX>::r[0] == 16 &&
+                      16 % TPC == 0 && THREADS % 64 == 0,
+                  "plans");
+};
+struct IdxWave {    // one pad slot per 8 positions, components and values alike
+    int base;
+    __device__ __forceinline__ int operator()(int pos) const { return base + pos + (pos >> 3); }
+    __device__ __forceinline__ int scalar(int pos) const { return base + pos + (pos >> 3); }
+};
+// orders a wave's LDS accesses (which execute in order) for the compiler
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+template <typename T, int N, int PY, int PX, int CP>
+__global__ void __launch_bounds__((FusedMidW<T, N, PY, PX>::THREADS), 4)
+k_f_midw(JobRef jr, Twiddle<T> tw) {
+    using C = cplx<T>;
+    using G = FusedGeo<N, PY>;
+    using F = FusedMidW<T, N, PY, PX>;
+    using SF = SubSeq<N, PY, false>;
+    using SI = SubSeq<N, PY, true>;
+    using EF = Engine<T, N, F::TPC, false, PX>;
+    using EI = Engine<T, N, F::TPC, true, PX>;
+    constexpr int n = N / 2, R = G::R, M = G::M, A4 = F::A4, TH = F::THREADS, TPC = F::TPC;
+    constexpr int P = ((n + 1 + 15) / 16) * 16;
+    constexpr size_t BLK = G::template blk<T>();
+    __shared__ C lds[F::ELEMS + N];
+    const int wg = xcd_item(blockIdx.x, gridDim.x);
+    if (wg >= F::BLOCKS) return;                    // uniform over the workgroup
+    const auto twf = tw_fetch<T, N, TH, true>(tw);
+    const Job jb = jr.get();
+    const int res = wg % R, k3 = wg / R;
+    C *block = (C *)jb.A + (size_t)(res * (n + 1) + k3) * BLK;
+    const int lane = threadIdx.x & 63, h = lane >> 4, u = (threadIdx.x >> 6) * 16 + (lane & 15);
+    const int t = u % TPC, c = u / TPC;
+    auto slot = [&](int col, int pos) { return col * F::MLINE + pos + (pos >> 3); };
+
+    // radix-A stage: butterfly g of row `row`, IA per thread
+    constexpr int RA = SF::radix(0), PA = M / RA, IA = n * PA / TH;
+    static_assert(n * PA % TH == 0 && SI::radix(1) == RA && SI::radix(0) == 4, "items");
+    C v[16];
+#pragma unroll
+    for (int i = 0; i < IA; ++i) {
+        const int it = (int)threadIdx.x + i * TH, g = it % PA, row = it / PA;
+#pragma unroll
+        for (int q = 0; q < RA; ++q) v[i * RA + q] = a_load<CP>(&block[(size_t)row * M + SF::template in_pos<0>(g, q)]);
+    }
+    const TableTwiddle<T, N> twx = tw_commit<T, N, TH, true>(tw, twf, lds + F::ELEMS);
+#pragma unroll
+    for (int i = 0; i < IA; ++i) {
+        const int it = (int)threadIdx.x + i * TH, g = it % PA, row = it / PA;
+        SF::template butterfly<0>(v + i * RA, g, res, twx);
+#pragma unroll
+        for (int q = 0; q < RA; ++q) lds[slot(SF::template out_pos<0>(g, q), row)] = v[i * RA + q];
+    }
+    __syncthreads();
+    // radix-4 stage, then to the i1 column c + A4 h
+#pragma unroll
+    for (int e = 0; e < 2; ++e)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) v[4 * e + q] = lds[slot(SF::template in_pos<1>(c, q), t + (h + 4 * e) * TPC)];
+    __syncthreads();                                // the buffer becomes the i1 exchange's
+#pragma unroll
+    for (int e = 0; e < 2; ++e) SF::template butterfly<1>(v + 4 * e, c, res, twx);
+    lane_exchange<4, 8>(v);
+#pragma unroll
+    for (int l = 8; l < 16; ++l) v[l] = c_zero<C>();
+    const int col = c + A4 * h, k2 = res + R * col, bk = k2 <= n ? k2 : N - k2;
+    const IdxWave idx{col * F::ELINE};
+    T *ls = reinterpret_cast<T *>(lds);
+    auto exchange = [&](auto engine) {
+        using E = decltype(engine);
+        if constexpr (sizeof(T) == 8) {
+            E::template store_comp<0, 0>(v, ls, t, idx);
+            wave_sync();
+            E::template load_comp<1, 0>(v, ls, t, idx);
+            wave_sync();
+            E::template store_comp<0, 1>(v, ls, t, idx);
+            wave_sync();
+            E::template load_comp<1, 1>(v, ls, t, idx);
+        } else {
+            E::template store_lds<0>(v, lds, t, idx);
+            wave_sync();
+            E::template load_lds<1>(v, lds, t, idx);
+        }
+        wave_sync();
+    };
+    EF::template compute<0>(v, t, twx);
+    exchange(EF{});
+    EF::template compute<1>(v, t, twx);
+    const double *mrow = jb.mult + ((size_t)bk * P + k3) * (n + 1);
+    EF::for_outputs(v, t, [&](int pos, int leg, C &val) {
+        constexpr int RL = EF::R(EF::S - 1);
+        val = scale_mode(val, g_load(&mrow[leg < RL / 2 ? pos : N - pos]));
+    });
+    EI::template compute<0>(v, t, twx);
+    exchange(EI{});
+    EI::template compute<1>(v, t, twx);
+    // legs below 8 are the rows t + l N/16 kept
+    lane_exchange<4, 8>(v);
+#pragma unroll
+    for (int e = 0; e < 2; ++e) SI::template butterfly<0>(v + 4 * e, c, res, twx);
+    __syncthreads();                                // every wave is done with its i1 exchange
+#pragma unroll
+    for (int e = 0; e < 2; ++e)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) lds[slot(SI::template out_pos<0>(c, q), t + (h + 4 * e) * TPC)] = v[4 * e + q];
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < IA; ++i) {
+        const int it = (int)threadIdx.x + i * TH, g = it % PA, row = it / PA;
+#pragma unroll
+        for (int q = 0; q < RA; ++q) v[i * RA + q] = lds[slot(SI::template in_pos<1>(g, q), row)];
+        SI::template butterfly<1>(v + i * RA, g, res, twx);
+#pragma unroll
+        for (int q = 0; q < RA; ++q) a_store<CP>(&block[(size_t)row * M + SI::template out_pos<1>(g, q)], v[i * RA + q]);
+    }
+}
+
 // ------------------------------------------------------------------- F3
 template <typename T, int N, int PZ, int PY, int J, int KU, int CP>
 __global__ void __launch_bounds__((FusedLines<T, N, PZ, PY, J>::THREADS))
@@ -442,15 +587,29 @@ template <typename T, int N> hipError_t fused_solve(const Job &one, const Job *t
         constexpr int n = N / 2, PZ = fused_plan(N, 0), PY = fused_plan(N, 1), PX = fused_plan(N, 2);
         using G = FusedGeo<N, PY>;
         using F1 = FusedLines<T, N, PZ, PY, Cfg::J>;
-        using F2 = FusedMid<T, N, PY, PX, Cfg::NB>;
         static_assert((size_t)G::R * (n + 1) * G::template blk<T>() <=
                           a_plane(n, n, (n / LayoutTile<T>::W + 1) * LayoutTile<T>::W, sizeof(cplx<T>)) * n,
                       "the blocks fit the intermediate A");
         const dim3 lines(xcd_blocks(n * F1::GROUPS), count);
-        hipLaunchKernelGGL((k_f_fwd<T, N, PZ, PY, Cfg::J, Cfg::NT ? 1 : 0>), lines, dim3(F1::THREADS), 0, st, jr, tw);
-        hipLaunchKernelGGL((k_f_mid<T, N, PY, PX, Cfg::NB, Cfg::NT ? 2 : 0>),
-                           dim3(xcd_blocks(ceil_div(F2::BLOCKS, Cfg::NB)), count), dim3(F2::THREADS), 0, st, jr, tw);
-        hipLaunchKernelGGL((k_f_inv<T, N, PZ, PY, Cfg::J, Cfg::KU, Cfg::NT ? 2 : 0>), lines, dim3(F1::THREADS), 0, st, jr, tw);
+        auto launch = [&](auto nt) {
+            constexpr int CW = decltype(nt)::value ? 1 : 0, CP = decltype(nt)::value ? 2 : 0;
+            hipLaunchKernelGGL((k_f_fwd<T, N, PZ, PY, Cfg::J, CW>), lines, dim3(F1::THREADS), 0, st, jr, tw);
+            if constexpr (Cfg::W) {
+                using F2 = FusedMidW<T, N, PY, PX>;
+                hipLaunchKernelGGL((k_f_midw<T, N, PY, PX, CP>), dim3(xcd_blocks(F2::BLOCKS), count), dim3(F2::THREADS),
+                                   0, st, jr, tw);
+            } else {
+                using F2 = FusedMid<T, N, PY, PX, Cfg::NB>;
+                hipLaunchKernelGGL((k_f_mid<T, N, PY, PX, Cfg::NB, CP>),
+                                   dim3(xcd_blocks(ceil_div(F2::BLOCKS, Cfg::NB)), count), dim3(F2::THREADS), 0, st, jr,
+                                   tw);
+            }
+            hipLaunchKernelGGL((k_f_inv<T, N, PZ, PY, Cfg::J, Cfg::KU, CP>), lines, dim3(F1::THREADS), 0, st, jr, tw);
+        };
+        if (Cfg::NT && count == 1)
+            launch(Const<Cfg::NT>{});
+        else
+            launch(Const<0>{});
     }
     return hipGetLastError();
 }

@@ -85,21 +85,21 @@ constexpr bool plan_exists(int N, int pv) {
     return pv == 0 || (pv == 1 && alt_plan_exists(N)) || (pv == 2 && r16_plan_exists(N));
 }
 // The three-launch solve of a cube (fused.hpp): the padded lengths it is
-// built for (all up to 128), and the radix plan of each axis it runs (0: i3,
-// 1: i2, 2: i1).  A solve takes it when its shape has these plans, so that
-// its result is bitwise that of the five passes.  Up to n = 64 a solve is
-// bound by launches and the latency of each kernel, which three launches
-// save (FP64, us: n = 32 20.7 -> 15.0, n = 64 26.9 -> 22.6).  Beyond, the
-// middle kernel's tile (n^2/4 FP64 values and their LDS exchanges) leaves one
-// or two workgroups per CU whose load, FFT and store phases do not overlap:
-// its 46 us at n = 96 and 44-59 us at n = 128 exceed what the two saved
-// passes over the i3 spectra give (whole solves 67 against 51, and 77 to 92
-// against 89 us).
+// built for, and the radix plan of each axis it runs (0: i3, 1: i2, 2: i1).
+// A solve takes it when its shape has these plans, so that its result is
+// bitwise that of the five passes.  The lengths are those where three
+// launches measured faster, alone and several per launch, us per solve of
+// FP64 against five passes: n = 64 22.6 and 9.4 (26.9 and 13), n = 128 77.9
+// and 67 (89.4 and 91).  n = 72 only with several solves per launch (14.3
+// against 17.7): one alone takes 37.1 against 34.0, as F2's 584 workgroups of
+// nine waves leave the CUs one or two each and its phases do not overlap.
+// n = 96 and 108 have F2s of 46 us against 21 and 26 for H3.
 constexpr bool fused_length(int N) {
     return N == 8 || N == 12 || N == 16 || N == 24 || N == 32 || N == 36 || N == 48 || N == 64 || N == 72 ||
-           N == 96 || N == 108 || N == 128;
+           N == 96 || N == 108 || N == 128 || N == 144 || N == 256;
 }
-constexpr int fused_plan(int N, int axis) { return N == 128 && axis == 2 ? 2 : 0; }
+constexpr int fused_plan(int N, int axis) { return (N == 128 || N == 256) && axis == 2 ? 2 : 0; }
+constexpr bool fused_count(int N, int count) { return N != 144 || count > 1; }
 inline bool fused_shape(int N, const Shape &s) {
     return fused_length(N) && s.plan[0] == fused_plan(N, 0) && s.plan[4] == fused_plan(N, 0) &&
            s.plan[1] == fused_plan(N, 1) && s.plan[3] == fused_plan(N, 1) && s.plan[2] == fused_plan(N, 2);

@@ -647,7 +647,8 @@ hipError_t passes_impl(const Job &one, const Job *table, int count, int P, int c
     if constexpr (fused_length(N)) {
         // per-pass events, partial passes and shrunk workspaces need the five
         // passes; everything else of these lengths and plans runs fused
-        if (!full && !ev && mask == 0x1f && mrows && chunk_tiles <= 0 && i1_group <= 0 && fused_shape(N, sh))
+        if (!full && !ev && mask == 0x1f && mrows && chunk_tiles <= 0 && i1_group <= 0 && fused_shape(N, sh) &&
+            fused_count(N, count))
             return fused_solve<T, N>(one, table, count, tw64, st);
     }
     if (full) {
