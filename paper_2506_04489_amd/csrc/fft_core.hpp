@@ -379,7 +379,7 @@ PSP_PLAN(48, 0, 4, 4, 3)
 PSP_PLAN(64, 0, 8, 8)
 PSP_PLAN(96, 0, 8, 4, 3)
 PSP_PLAN(128, 0, 8, 4, 4)
-PSP_PLAN(192, 0, 8, 8, 3)
+PSP_PLAN(192, 0, 8, 6, 4)
 PSP_PLAN(256, 0, 8, 8, 4)
 PSP_PLAN(384, 0, 8, 4, 4, 3)
 PSP_PLAN(512, 0, 8, 8, 8)
@@ -412,7 +412,7 @@ PSP_PLAN(768, 1, 12, 8, 8)
 // radix-16 alternatives (radix 12 for 768): one FFT stage (and LDS exchange)
 // fewer where the length allows it
 PSP_PLAN(128, 2, 16, 8)
-PSP_PLAN(192, 2, 16, 4, 3)
+PSP_PLAN(192, 2, 16, 12)
 PSP_PLAN(256, 2, 16, 16)
 PSP_PLAN(384, 2, 16, 8, 3)
 PSP_PLAN(512, 2, 16, 8, 4)

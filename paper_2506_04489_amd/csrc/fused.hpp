@@ -19,7 +19,8 @@
 // theirs.  These sizes are bound by launches (three empty ones in a row take
 // 7.5 us) and by the chain of latencies inside each kernel; solves went from
 // five launches to, FP64 us per solve, 15.0 (from 20.7) at n = 16 and 32,
-// 21.0 (24.8) at n = 48, 22.6 (26.9) at n = 64, 77.9 (89.4) at n = 128; FP32
+// 21.0 (24.8) at n = 48, 22.6 (26.9) at n = 64, 48.0 (51.4) at n = 96, 77.9
+// (89.4) at n = 128; FP32
 // 18.8 (23.5) at n = 64, 50.5 (56.0) at n = 128.  Large ones are bound by F2
 // (42 of 75 us at n = 128), whose exchanges go through LDS; k_f_midw, which
 // does two of six in registers, took it from 59 us.
@@ -82,15 +83,17 @@ constexpr int SINGLE_MAX = 16;
 // Tile of the fused kernels: J columns per workgroup of F1 and F3, KU bins
 // per thread and round of F3, NB blocks per workgroup of F2.
 template <typename T, int N> struct FusedCfg {
-    static constexpr int J = N == 36 ? 2 : N == 108 ? 6 : N == 256 ? 8 : 4;
-    static constexpr int KU = N == 256 ? 1 : N == 144 ? 2 : 3;
+    static constexpr int J = N == 36 ? 2 : N == 108 ? 6 : N == 256 ? 8 : N == 192 ? (sizeof(T) == 8 ? 12 : 8) : 4;
+    static constexpr int KU = N == 256 ? 1 : N == 144 || N == 192 ? 2 : 3;
+    // J and KU of F3 with several solves per launch
+    static constexpr int JM = N == 192 && sizeof(T) == 8 ? 4 : J, KUM = JM == J ? KU : 3;
     static constexpr int NB = N <= 32 ? 4 : N == 36 ? 2 : 1;
     // the 17 MB of A of one solve at n = 64 FP64 written and read past the
     // caches: 26.7 -> 24.2 us for the three launches (other sizes and several
     // solves in one launch lose by it, n = 128 74 -> 84 us)
     static constexpr bool NT = N == 128 && sizeof(T) == 8;
     // whether the plans fit k_f_midw
-    static constexpr bool W = N == 128 || N == 256;
+    static constexpr bool W = N == 128 || N == 192 || N == 256;
 };
 
 // consecutive work items on one XCD (workgroups go to the 8 XCDs in turn):
@@ -367,18 +370,21 @@ k_f_mid(JobRef jr, Twiddle<T> tw) {
 // + A h, whose first-stage legs are the rows t + l N/16 of all four h.  With h
 // in lane bits 4 and 5 that is a swap of register with lane bits.  The
 // threads t of a column are lanes of one wave, so the i1 exchange needs no
-// workgroup barrier.  k_f_mid moved every value through LDS six times between
+// workgroup barrier.  At N = 192 only 12 of a column's 16 lanes hold rows (the
+// second i1 stage has 16 butterflies and uses all); five waves per SIMD, for a
+// third workgroup per CU, spill 62 registers there (25 -> 39 us).  k_f_mid moved every value through LDS six times between
 // twelve barriers, this moves it four times between five.
 template <typename T, int N, int PY, int PX> struct FusedMidW {
     using G = FusedGeo<N, PY>;
-    static constexpr int TPC = N / 16, A4 = G::M / 4, THREADS = G::M * TPC;
+    static constexpr int NT = N / 16, TPC = NT <= 8 ? 8 : 16;   // threads t that hold rows; lanes of a column
+    static constexpr int A4 = G::M / 4, THREADS = G::M * TPC;
     static constexpr int ELINE = N + N / 8 + 1;                 // column of the i1 exchange: scalars in FP64, values in FP32
     static constexpr int MLINE = (N / 2 * 9 / 8) | 1;           // column of the M-point exchange, values
     static constexpr int ES = G::M * ELINE / (sizeof(T) == 8 ? 2 : 1) + 1;
     static constexpr int ELEMS = ES > G::M * MLINE ? ES : G::M * MLINE;
     static constexpr int BLOCKS = G::R * (N / 2 + 1);
     static_assert(Plan<N, PY>::S == 3 && Plan<N, PY>::r[2] == 4 && Plan<N, PX>::S == 2 && Plan<N, PX>::r[0] == 16 &&
-                      16 % TPC == 0 && THREADS % 64 == 0,
+                      NT <= 16 && THREADS % 64 == 0,
                   "plans");
 };
 struct IdxWave {    // one pad slot per 8 positions, components and values alike
@@ -402,7 +408,7 @@ k_f_midw(JobRef jr, Twiddle<T> tw) {
     using SI = SubSeq<N, PY, true>;
     using EF = Engine<T, N, F::TPC, false, PX>;
     using EI = Engine<T, N, F::TPC, true, PX>;
-    constexpr int n = N / 2, R = G::R, M = G::M, A4 = F::A4, TH = F::THREADS, TPC = F::TPC;
+    constexpr int n = N / 2, R = G::R, M = G::M, A4 = F::A4, TH = F::THREADS, TPC = F::TPC, NT = F::NT;
     constexpr int P = ((n + 1 + 15) / 16) * 16;
     constexpr size_t BLK = G::template blk<T>();
     __shared__ C lds[F::ELEMS + N];
@@ -414,6 +420,7 @@ k_f_midw(JobRef jr, Twiddle<T> tw) {
     C *block = (C *)jb.A + (size_t)(res * (n + 1) + k3) * BLK;
     const int lane = threadIdx.x & 63, h = lane >> 4, u = (threadIdx.x >> 6) * 16 + (lane & 15);
     const int t = u % TPC, c = u / TPC;
+    const bool on = NT == TPC || t < NT;
     auto slot = [&](int col, int pos) { return col * F::MLINE + pos + (pos >> 3); };
 
     // radix-A stage: butterfly g of row `row`, IA per thread
@@ -439,7 +446,10 @@ k_f_midw(JobRef jr, Twiddle<T> tw) {
 #pragma unroll
     for (int e = 0; e < 2; ++e)
 #pragma unroll
-        for (int q = 0; q < 4; ++q) v[4 * e + q] = lds[slot(SF::template in_pos<1>(c, q), t + (h + 4 * e) * TPC)];
+        for (int q = 0; q < 4; ++q) {
+            v[4 * e + q] = c_zero<C>();
+            if (on) v[4 * e + q] = lds[slot(SF::template in_pos<1>(c, q), t + (h + 4 * e) * NT)];
+        }
     __syncthreads();                                // the buffer becomes the i1 exchange's
 #pragma unroll
     for (int e = 0; e < 2; ++e) SF::template butterfly<1>(v + 4 * e, c, res, twx);
@@ -485,7 +495,8 @@ k_f_midw(JobRef jr, Twiddle<T> tw) {
 #pragma unroll
     for (int e = 0; e < 2; ++e)
 #pragma unroll
-        for (int q = 0; q < 4; ++q) lds[slot(SI::template out_pos<0>(c, q), t + (h + 4 * e) * TPC)] = v[4 * e + q];
+        for (int q = 0; q < 4; ++q)
+            if (on) lds[slot(SI::template out_pos<0>(c, q), t + (h + 4 * e) * NT)] = v[4 * e + q];
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < IA; ++i) {
@@ -590,10 +601,12 @@ template <typename T, int N> hipError_t fused_solve(const Job &one, const Job *t
         static_assert((size_t)G::R * (n + 1) * G::template blk<T>() <=
                           a_plane(n, n, (n / LayoutTile<T>::W + 1) * LayoutTile<T>::W, sizeof(cplx<T>)) * n,
                       "the blocks fit the intermediate A");
-        const dim3 lines(xcd_blocks(n * F1::GROUPS), count);
-        auto launch = [&](auto nt) {
-            constexpr int CW = decltype(nt)::value ? 1 : 0, CP = decltype(nt)::value ? 2 : 0;
-            hipLaunchKernelGGL((k_f_fwd<T, N, PZ, PY, Cfg::J, CW>), lines, dim3(F1::THREADS), 0, st, jr, tw);
+        auto launch = [&](auto many) {
+            constexpr bool MANY = decltype(many)::value, NT = Cfg::NT && !MANY;
+            constexpr int CW = NT ? 1 : 0, CP = NT ? 2 : 0, J3 = MANY ? Cfg::JM : Cfg::J, KU = MANY ? Cfg::KUM : Cfg::KU;
+            using F3 = FusedLines<T, N, PZ, PY, J3>;
+            hipLaunchKernelGGL((k_f_fwd<T, N, PZ, PY, Cfg::J, CW>), dim3(xcd_blocks(n * F1::GROUPS), count),
+                               dim3(F1::THREADS), 0, st, jr, tw);
             if constexpr (Cfg::W) {
                 using F2 = FusedMidW<T, N, PY, PX>;
                 hipLaunchKernelGGL((k_f_midw<T, N, PY, PX, CP>), dim3(xcd_blocks(F2::BLOCKS), count), dim3(F2::THREADS),
@@ -604,10 +617,11 @@ template <typename T, int N> hipError_t fused_solve(const Job &one, const Job *t
                                    dim3(xcd_blocks(ceil_div(F2::BLOCKS, Cfg::NB)), count), dim3(F2::THREADS), 0, st, jr,
                                    tw);
             }
-            hipLaunchKernelGGL((k_f_inv<T, N, PZ, PY, Cfg::J, Cfg::KU, CP>), lines, dim3(F1::THREADS), 0, st, jr, tw);
+            hipLaunchKernelGGL((k_f_inv<T, N, PZ, PY, J3, KU, CP>), dim3(xcd_blocks(n * F3::GROUPS), count),
+                               dim3(F3::THREADS), 0, st, jr, tw);
         };
-        if (Cfg::NT && count == 1)
-            launch(Const<Cfg::NT>{});
+        if (count > 1)
+            launch(Const<1>{});
         else
             launch(Const<0>{});
     }

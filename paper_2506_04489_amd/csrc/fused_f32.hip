@@ -18,6 +18,7 @@ PSP_FUSED(96)
 PSP_FUSED(108)
 PSP_FUSED(128)
 PSP_FUSED(144)
+PSP_FUSED(192)
 PSP_FUSED(256)
 #undef PSP_FUSED
 

@@ -89,17 +89,19 @@ constexpr bool plan_exists(int N, int pv) {
 // A solve takes it when its shape has these plans, so that its result is
 // bitwise that of the five passes.  The lengths are those where three
 // launches measured faster, alone and several per launch, us per solve of
-// FP64 against five passes: n = 64 22.6 and 9.4 (26.9 and 13), n = 128 77.9
-// and 67 (89.4 and 91).  n = 72 only with several solves per launch (14.3
-// against 17.7): one alone takes 37.1 against 34.0, as F2's 584 workgroups of
-// nine waves leave the CUs one or two each and its phases do not overlap.
-// n = 96 and 108 have F2s of 46 us against 21 and 26 for H3.
+// FP64 against five passes: n = 64 22.6 and 9.4 (26.9 and 13), n = 96 48.0
+// and 38.0 (51.4 and 41.6), n = 128 77.9 and 67 (89.4 and 91).  n = 72 only
+// with several solves per launch (14.3 against 17.7): one alone takes 37.1
+// against 34.0, as F2's 584 workgroups of nine waves leave the CUs one or two
+// each and its phases do not overlap.  For the same reason n = 96 in FP32
+// (20.1 against 24.9 for several, one alone 39.1 against 36.3).  n = 108 has
+// an F2 of 46 us against 26 for H3.
 constexpr bool fused_length(int N) {
     return N == 8 || N == 12 || N == 16 || N == 24 || N == 32 || N == 36 || N == 48 || N == 64 || N == 72 ||
-           N == 96 || N == 108 || N == 128 || N == 144 || N == 256;
+           N == 96 || N == 108 || N == 128 || N == 144 || N == 192 || N == 256;
 }
-constexpr int fused_plan(int N, int axis) { return (N == 128 || N == 256) && axis == 2 ? 2 : 0; }
-constexpr bool fused_count(int N, int count) { return N != 144 || count > 1; }
+constexpr int fused_plan(int N, int axis) { return (N == 128 || N == 192 || N == 256) && axis == 2 ? 2 : 0; }
+constexpr bool fused_count(int N, bool f64, int count) { return count > 1 || !(N == 144 || (N == 192 && !f64)); }
 inline bool fused_shape(int N, const Shape &s) {
     return fused_length(N) && s.plan[0] == fused_plan(N, 0) && s.plan[4] == fused_plan(N, 0) &&
            s.plan[1] == fused_plan(N, 1) && s.plan[3] == fused_plan(N, 1) && s.plan[2] == fused_plan(N, 2);

@@ -648,7 +648,7 @@ hipError_t passes_impl(const Job &one, const Job *table, int count, int P, int c
         // per-pass events, partial passes and shrunk workspaces need the five
         // passes; everything else of these lengths and plans runs fused
         if (!full && !ev && mask == 0x1f && mrows && chunk_tiles <= 0 && i1_group <= 0 && fused_shape(N, sh) &&
-            fused_count(N, count))
+            fused_count(N, sizeof(T) == 8, count))
             return fused_solve<T, N>(one, table, count, tw64, st);
     }
     if (full) {

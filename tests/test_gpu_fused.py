@@ -1,4 +1,4 @@
-"""The three-launch solve of cubes with n <= 72 and n = 128 (fused.hpp): bitwise equal to
+"""The three-launch solve of cubes with n <= 72, 96 and 128 (fused.hpp): bitwise equal to
 the five passes at every length it is built for, in both tiers, on inputs of
 full power.  Five passes run when the solve records per-pass events, when k3
 runs in chunks, or when a radix plan differs from the fused one."""
@@ -10,7 +10,7 @@ from tests.gpu_util import announce, rel_max_err
 
 pytestmark = pytest.mark.gpu
 
-FUSED = [4, 6, 8, 12, 16, 18, 24, 32, 36, 48, 54, 64, 72, 128]
+FUSED = [4, 6, 8, 12, 16, 18, 24, 32, 36, 48, 54, 64, 72, 96, 128]
 
 
 @pytest.fixture(autouse=True)
