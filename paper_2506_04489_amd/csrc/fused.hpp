@@ -19,10 +19,10 @@
 // theirs.  These sizes are bound by launches (three empty ones in a row take
 // 7.5 us) and by the chain of latencies inside each kernel; solves went from
 // five launches to, FP64 us per solve, 15.0 (from 20.7) at n = 16 and 32,
-// 21.0 (24.8) at n = 48, 22.6 (26.9) at n = 64, 48.0 (51.4) at n = 96, 77.9
+// 21.0 (24.8) at n = 48, 22.6 (26.9) at n = 64, 47.8 (51.4) at n = 96, 76.4
 // (89.4) at n = 128; FP32
-// 18.8 (23.5) at n = 64, 50.5 (56.0) at n = 128.  Large ones are bound by F2
-// (42 of 75 us at n = 128), whose exchanges go through LDS; k_f_midw, which
+// 18.8 (23.5) at n = 64, 50.0 (56.0) at n = 128.  Large ones are bound by F2
+// (39 of 72 us at n = 128), whose exchanges go through LDS; k_f_midw, which
 // does two of six in registers, took it from 59 us.
 //
 // A holds R (n + 1) blocks [r][k3] of n rows i1 of M columns j (block pitch
@@ -378,19 +378,28 @@ template <typename T, int N, int PY, int PX> struct FusedMidW {
     using G = FusedGeo<N, PY>;
     static constexpr int NT = N / 16, TPC = NT <= 8 ? 8 : 16;   // threads t that hold rows; lanes of a column
     static constexpr int A4 = G::M / 4, THREADS = G::M * TPC;
-    static constexpr int ELINE = N + N / 8 + 1;                 // column of the i1 exchange: scalars in FP64, values in FP32
-    static constexpr int MLINE = (N / 2 * 9 / 8) | 1;           // column of the M-point exchange, values
-    static constexpr int ES = G::M * ELINE / (sizeof(T) == 8 ? 2 : 1) + 1;
-    static constexpr int ELEMS = ES > G::M * MLINE ? ES : G::M * MLINE;
+    // Pitches that keep the lanes served together on different banks.  The i1
+    // exchange (scalars in FP64, values in FP32): a pad slot per 16 positions,
+    // and columns of lane groups h and h + 1 offset by half the banks.  The
+    // M-point exchange (values): four neighbouring columns by two or four
+    // rows, whether the columns are adjacent or A apart.  With a pad slot per
+    // 8 positions and odd pitches in both, n = 128 FP64 took 42.1 us alone and
+    // 35.4 several per launch, now 39.4 and 30.9.
+    static constexpr int ELINE = N + N / 16, EH = N == 192 ? 8 : 16;
+    static constexpr int ES = (G::M * ELINE + 3 * EH) / (sizeof(T) == 8 ? 2 : 1) + 1;
+    static constexpr int MLINE = N / 2 + (N == 192 ? 6 : 4), MA = N == 192 ? 0 : 4;
+    static_assert(N / 2 % 16 == 0, "pitch");
+    static constexpr int MS = G::M * MLINE + 3 * MA;
+    static constexpr int ELEMS = ES > MS ? ES : MS;
     static constexpr int BLOCKS = G::R * (N / 2 + 1);
     static_assert(Plan<N, PY>::S == 3 && Plan<N, PY>::r[2] == 4 && Plan<N, PX>::S == 2 && Plan<N, PX>::r[0] == 16 &&
                       NT <= 16 && THREADS % 64 == 0,
                   "plans");
 };
-struct IdxWave {    // one pad slot per 8 positions, components and values alike
+struct IdxWave {    // one pad slot per 16 positions, components and values alike
     int base;
-    __device__ __forceinline__ int operator()(int pos) const { return base + pos + (pos >> 3); }
-    __device__ __forceinline__ int scalar(int pos) const { return base + pos + (pos >> 3); }
+    __device__ __forceinline__ int operator()(int pos) const { return base + pos + (pos >> 4); }
+    __device__ __forceinline__ int scalar(int pos) const { return base + pos + (pos >> 4); }
 };
 // orders a wave's LDS accesses (which execute in order) for the compiler
 __device__ __forceinline__ void wave_sync() {
@@ -421,7 +430,7 @@ k_f_midw(JobRef jr, Twiddle<T> tw) {
     const int lane = threadIdx.x & 63, h = lane >> 4, u = (threadIdx.x >> 6) * 16 + (lane & 15);
     const int t = u % TPC, c = u / TPC;
     const bool on = NT == TPC || t < NT;
-    auto slot = [&](int col, int pos) { return col * F::MLINE + pos + (pos >> 3); };
+    auto slot = [&](int col, int pos) { return col * F::MLINE + (col / (M / 4)) * F::MA + pos; };
 
     // radix-A stage: butterfly g of row `row`, IA per thread
     constexpr int RA = SF::radix(0), PA = M / RA, IA = n * PA / TH;
@@ -457,7 +466,7 @@ k_f_midw(JobRef jr, Twiddle<T> tw) {
 #pragma unroll
     for (int l = 8; l < 16; ++l) v[l] = c_zero<C>();
     const int col = c + A4 * h, k2 = res + R * col, bk = k2 <= n ? k2 : N - k2;
-    const IdxWave idx{col * F::ELINE};
+    const IdxWave idx{col * F::ELINE + F::EH * h};
     T *ls = reinterpret_cast<T *>(lds);
     auto exchange = [&](auto engine) {
         using E = decltype(engine);

@@ -89,8 +89,8 @@ constexpr bool plan_exists(int N, int pv) {
 // A solve takes it when its shape has these plans, so that its result is
 // bitwise that of the five passes.  The lengths are those where three
 // launches measured faster, alone and several per launch, us per solve of
-// FP64 against five passes: n = 64 22.6 and 9.4 (26.9 and 13), n = 96 48.0
-// and 38.0 (51.4 and 41.6), n = 128 77.9 and 67 (89.4 and 91).  n = 72 only
+// FP64 against five passes: n = 64 22.6 and 9.0 (26.9 and 13), n = 96 47.8
+// and 37.6 (51.4 and 41.6), n = 128 76.4 and 64 (89.4 and 91).  n = 72 only
 // with several solves per launch (14.3 against 17.7): one alone takes 37.1
 // against 34.0, as F2's 584 workgroups of nine waves leave the CUs one or two
 // each and its phases do not overlap.  For the same reason n = 96 in FP32
