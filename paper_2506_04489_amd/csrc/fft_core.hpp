@@ -611,6 +611,16 @@ template <typename T, int N, int TPC, bool INV, int PV = 0> struct Engine {
         }
     }
 
+    // slot of the component at position pos in the exchange after stage s, which
+    // is value rem of the block q of positions that the stage fills from one
+    // group of butterflies.  Both sides know q and rem up to a constant per
+    // leg, so that most addresses are one register and an immediate offset
+    // where the layout goes by blocks.
+    template <int s, typename Idx> __device__ __forceinline__ static int scalar_slot(Idx idx, int pos, int q, int rem) {
+        if constexpr (Idx::template blocked<NS(s)>()) return idx.template block<NS(s), NS(s) * R(s)>(q, rem);
+        else return idx.scalar(pos);
+    }
+
     // component-wise exchange: COMP 0 moves the real parts, 1 the imaginary
     // parts, through a buffer of N scalars per column
     template <int s, int COMP, typename Idx>
@@ -621,7 +631,8 @@ template <typename T, int N, int TPC, bool INV, int PV = 0> struct Engine {
             const int j = t + b * TPC;
             if ((nb % TPC == 0) || j < nb) {
 #pragma unroll
-                for (int r = 0; r < r_; ++r) lds[idx.scalar(out_pos<s>(j, r))] = COMP ? v[b * r_ + r].y : v[b * r_ + r].x;
+                for (int r = 0; r < r_; ++r)
+                    lds[scalar_slot<s>(idx, out_pos<s>(j, r), j / NS(s), j % NS(s) + r * NS(s))] = COMP ? v[b * r_ + r].y : v[b * r_ + r].x;
             }
         }
     }
@@ -634,7 +645,7 @@ template <typename T, int N, int TPC, bool INV, int PV = 0> struct Engine {
             if ((nb % TPC == 0) || j < nb) {
 #pragma unroll
                 for (int r = 0; r < r_; ++r) {
-                    const T x = lds[idx.scalar(in_pos<s>(j, r))];
+                    const T x = lds[scalar_slot<s - 1>(idx, in_pos<s>(j, r), j / NS(s) + r * (N / r_ / NS(s)), j % NS(s))];
                     if (COMP) v[b * r_ + r].y = x;
                     else v[b * r_ + r].x = x;
                 }
@@ -690,8 +701,9 @@ template <typename T, int N, int TPC, bool INV, int PV = 0> struct Engine {
 #pragma unroll
                     for (int r = 0; r < LB; ++r) {
                         const int pos = in_pos<1>(lane_a<W>(t, i) + LA * lane_b<W>(t), r);
-                        if constexpr (decltype(part)::value == 0) v[i * LB + r].x = l[idx.scalar(pos)];
-                        else if constexpr (decltype(part)::value == 1) v[i * LB + r].y = l[idx.scalar(pos)];
+                        const int sc = scalar_slot<0>(idx, pos, lane_b<W>(t) + r * (N / LB / LA), lane_a<W>(t, i));
+                        if constexpr (decltype(part)::value == 0) v[i * LB + r].x = l[sc];
+                        else if constexpr (decltype(part)::value == 1) v[i * LB + r].y = l[sc];
                         else v[i * LB + r] = lds[idx(pos)];
                     }
             };
@@ -735,8 +747,9 @@ template <typename T, int N, int TPC, bool INV, int PV = 0> struct Engine {
 #pragma unroll
                     for (int r = 0; r < LB; ++r) {
                         const int pos = out_pos<1>(lane_a<W>(t, i) * LL + lane_b<W>(t), r);
-                        if constexpr (decltype(part)::value == 0) l[idx.scalar(pos)] = v[i * LB + r].x;
-                        else if constexpr (decltype(part)::value == 1) l[idx.scalar(pos)] = v[i * LB + r].y;
+                        const int sc = scalar_slot<1>(idx, pos, lane_a<W>(t, i), lane_b<W>(t) + r * LL);
+                        if constexpr (decltype(part)::value == 0) l[sc] = v[i * LB + r].x;
+                        else if constexpr (decltype(part)::value == 1) l[sc] = v[i * LB + r].y;
                         else lds[idx(pos)] = v[i * LB + r];
                     }
             };

@@ -85,8 +85,12 @@ constexpr int SINGLE_MAX = 16;
 template <typename T, int N> struct FusedCfg {
     static constexpr int J = N == 36 ? 2 : N == 108 ? 6 : N == 256 ? 8 : N == 192 ? (sizeof(T) == 8 ? 12 : 8) : 4;
     static constexpr int KU = N == 256 ? 1 : N == 144 || N == 192 ? 2 : 3;
-    // J and KU of F3 with several solves per launch
-    static constexpr int JM = N == 192 && sizeof(T) == 8 ? 4 : J, KUM = JM == J ? KU : 3;
+    // J of F1 and of F3, KU of F3, with several solves per launch: there are
+    // workgroups enough for wider rows of A (n = 64 7.34 -> 7.16 us per solve,
+    // FP32 4.69 -> 4.38; n = 128 FP32 40.1 -> 37.9; n = 72 15.7 -> 15.0)
+    static constexpr int J1M = N == 128 ? 8 : N == 256 && sizeof(T) == 4 ? 16 : N == 144 ? 12 : J;
+    static constexpr int J3M = N == 128 ? 8 : N == 192 && sizeof(T) == 8 ? 4 : N == 144 ? 12 : J;
+    static constexpr int KUM = N == 128 ? 2 : N == 192 && sizeof(T) == 8 ? 3 : N == 144 ? 1 : KU;
     static constexpr int NB = N <= 32 ? 4 : N == 36 ? 2 : 1;
     // the 17 MB of A of one solve at n = 64 FP64 written and read past the
     // caches: 26.7 -> 24.2 us for the three launches (other sizes and several
@@ -400,6 +404,7 @@ struct IdxWave {    // one pad slot per 16 positions, components and values alik
     int base;
     __device__ __forceinline__ int operator()(int pos) const { return base + pos + (pos >> 4); }
     __device__ __forceinline__ int scalar(int pos) const { return base + pos + (pos >> 4); }
+    template <int> static constexpr bool blocked() { return false; }
 };
 // orders a wave's LDS accesses (which execute in order) for the compiler
 __device__ __forceinline__ void wave_sync() {
@@ -606,15 +611,16 @@ template <typename T, int N> hipError_t fused_solve(const Job &one, const Job *t
         using Cfg = FusedCfg<T, N>;
         constexpr int n = N / 2, PZ = fused_plan(N, 0), PY = fused_plan(N, 1), PX = fused_plan(N, 2);
         using G = FusedGeo<N, PY>;
-        using F1 = FusedLines<T, N, PZ, PY, Cfg::J>;
         static_assert((size_t)G::R * (n + 1) * G::template blk<T>() <=
                           a_plane(n, n, (n / LayoutTile<T>::W + 1) * LayoutTile<T>::W, sizeof(cplx<T>)) * n,
                       "the blocks fit the intermediate A");
         auto launch = [&](auto many) {
             constexpr bool MANY = decltype(many)::value, NT = Cfg::NT && !MANY;
-            constexpr int CW = NT ? 1 : 0, CP = NT ? 2 : 0, J3 = MANY ? Cfg::JM : Cfg::J, KU = MANY ? Cfg::KUM : Cfg::KU;
+            constexpr int CW = NT ? 1 : 0, CP = NT ? 2 : 0, J1 = MANY ? Cfg::J1M : Cfg::J, J3 = MANY ? Cfg::J3M : Cfg::J,
+                          KU = MANY ? Cfg::KUM : Cfg::KU;
+            using F1 = FusedLines<T, N, PZ, PY, J1>;
             using F3 = FusedLines<T, N, PZ, PY, J3>;
-            hipLaunchKernelGGL((k_f_fwd<T, N, PZ, PY, Cfg::J, CW>), dim3(xcd_blocks(n * F1::GROUPS), count),
+            hipLaunchKernelGGL((k_f_fwd<T, N, PZ, PY, J1, CW>), dim3(xcd_blocks(n * F1::GROUPS), count),
                                dim3(F1::THREADS), 0, st, jr, tw);
             if constexpr (Cfg::W) {
                 using F2 = FusedMidW<T, N, PY, PX>;

@@ -74,11 +74,34 @@ template <int W> struct IdxInter {   // (position, column) -> position*W + colum
     __device__ __forceinline__ int scalar(int pos) const {
         return ((pos & ~3) | ((pos ^ (pos >> 3)) & 3)) * W + col;
     }
+    // The same by blocks: value rem of block q of B positions, filled by
+    // butterflies whose outputs are NS apart.  A wave serves G neighbouring
+    // threads of all columns at a time.  With NS = 1 they store to G blocks,
+    // whose rows the low bits of q spread over the banks; with NS >= G their
+    // rows are adjacent as they are.  Only per-thread values and a constant
+    // per leg enter, where scalar() takes four instructions per access (n = 384
+    // FP64 H3: 2493 -> 2175 VALU instructions per wave), and blocks of 12 or 18
+    // spread as well as those of 8.  H3 alone, same shapes: n = 192 133 -> 127
+    // us, n = 216 315 -> 237, n = 288 469 -> 443, n = 256 251 -> 250, n = 324
+    // 821 -> 822, n = 384 1105 -> 1102.
+    static constexpr int G = 32 / W;
+    template <int NS> static constexpr bool blocked() { return NS == 1 || NS >= G; }
+    template <int NS, int B> __device__ __forceinline__ int block(int q, int rem) const {
+        if constexpr (NS > 1) {
+            return (q * B + rem) * W + col;
+        } else {
+            constexpr int lg = G == 8 ? 3 : G == 4 ? 2 : 1;
+            constexpr int k = B % 8 == 0 && lg > 2 ? 3 : B % 4 == 0 && lg > 1 ? 2 : B % 2 == 0 ? 1 : 0, m = (1 << k) - 1;
+            const int x = (q >> (lg - k)) & m;
+            return (q * B + ((rem & m) ^ x)) * W + col + (rem & ~m) * W;
+        }
+    }
 };
 struct IdxLine {                     // column-major, one padding slot per 8 positions
     int base;
     __device__ __forceinline__ int operator()(int pos) const { return base + pos + (pos >> 3); }
     __device__ __forceinline__ int scalar(int pos) const { return base + pos + (pos >> 3); }
+    template <int> static constexpr bool blocked() { return false; }
 };
 
 // Plain accesses to the solve's buffers, all global memory, made through
