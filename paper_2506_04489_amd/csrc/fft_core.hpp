@@ -563,14 +563,21 @@ template <typename T, int N, int TPC, bool INV, int PV = 0> struct Engine {
     template <int s, typename Idx>
     __device__ __forceinline__ static void store_half(const C *v, C *lds, int t, Idx idx, int ph) {
         constexpr int r_ = R(s), nb = N / r_;
+        // Butterflies j < nb / 2 store to the lower half: known per b, except
+        // in the middle one of an odd number.  A comparison per value took a
+        // branch each and kept both addresses alive (n = 384 FP32 H3, plan 12
+        // 8 8: 127 -> 116 registers, 742 -> 718 us; 8 8 12: 957 -> 706 us).
+        constexpr bool whole = nb % TPC == 0 && (nb / NS(s)) % 2 == 0;
 #pragma unroll
         for (int b = 0; b < BPT(s); ++b) {
             const int j = t + b * TPC;
             if ((nb % TPC == 0) || j < nb) {
+                const bool up = 2 * b >= BPT(s) || (2 * b + 2 > BPT(s) && j >= nb / 2);
+                if (whole && up != (ph == 1)) continue;
 #pragma unroll
                 for (int r = 0; r < r_; ++r) {
                     const int pos = out_pos<s>(j, r);
-                    if ((pos >= N / 2) == (ph == 1)) lds[idx(pos - ph * (N / 2))] = v[b * r_ + r];
+                    if (whole || (pos >= N / 2) == (ph == 1)) lds[idx(pos - ph * (N / 2))] = v[b * r_ + r];
                 }
             }
         }
