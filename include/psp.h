@@ -270,9 +270,10 @@ psp_status psp_plan_spectrum_bytes(const psp_plan *p, size_t *bytes);
 /* Per-pass device timing.  psp_profile_enable makes the next `max_solves`
  * psp_solve calls of this plan record 6 HIP events on their own stream:
  * before each of the 5 passes (forward i3, forward i2, fused i1 with the
- * multiply, inverse i2, inverse i3) and after the last (a cube with n <= 64, n = 96 or n = 128,
- * whose solve otherwise takes three launches with the same result, runs as
- * five passes while it is profiled).  psp_profile_read
+ * multiply, inverse i2, inverse i3) and after the last (a cube with n <= 64,
+ * n = 96 or n = 128, whose solve otherwise takes one or three launches with
+ * the same result, runs as five passes while it is profiled).
+ * psp_profile_read
  * waits for them and returns the number of recorded solves and the average
  * milliseconds of each pass (pass_ms[0..4]) and of the whole solve
  * (pass_ms[5]); it then clears the recording.  pass_ms has 6 entries. */
