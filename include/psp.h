@@ -230,13 +230,20 @@ psp_status psp_plan_set_tuning(psp_plan *p, int k3_tiles, int i1_group);
  * values move between stages and the accesses' cache policy: the results
  * are bitwise the same.  A radix plan changes the rounding, not the
  * accuracy class.  Batched solves and graphs group their members by (n,
- * shape).  Set: PSP_EINVAL for a value out of range; call it while no solve
+ * shape).  A plan whose shape was set here runs the five passes it
+ * describes; otherwise a cube that has a solve in three launches (n <= 64,
+ * 72, 96, 128) or one (n <= 8) takes that where its shape's radix plans are
+ * the ones built for it, with bitwise the result of the five passes, and the
+ * tiles apply only to its solves in five: profiled ones, k3 chunks, i1
+ * groups, persistent batches, a single solve with n = 72 or, in FP32, n = 96.
+ * Set: PSP_EINVAL for a value out of range; call it while no solve
  * of this plan is in flight.  Get: copies the plan's current shape. */
 psp_status psp_plan_set_shape(psp_plan *p, const int *plan, const int *tile);
 psp_status psp_plan_get_shape(const psp_plan *p, int *plan, int *tile);
 
 /* The process-wide tuning table: the shape that plans of (n, dtype) created
- * afterwards start with (and the serving loop's plans use).  Unset entries
+ * afterwards start with (and the serving loop's plans use); entries do not
+ * ask for the five passes as psp_plan_set_shape does.  Unset entries
  * give the default shape (all zeros).  psp_tuning_get reports it. */
 psp_status psp_tuning_set(int n, psp_dtype dtype, const int *plan, const int *tile);
 psp_status psp_tuning_get(int n, psp_dtype dtype, int *plan, int *tile);

@@ -63,17 +63,20 @@ __host__ __device__ constexpr size_t a_plane(int n1, int n2, int pa, int elem) {
 struct Shape {
     int plan[kPasses] = {0, 0, 0, 0, 0};
     int tile[kPasses] = {0, 0, 0, 0, 0};
+    // the five passes with these tiles also where a cube's three launches (or
+    // one) would give the same bits: a shape that psp_plan_set_shape set
+    bool five = false;
     bool operator==(const Shape &o) const {
         for (int p = 0; p < kPasses; ++p)
             if (plan[p] != o.plan[p] || tile[p] != o.tile[p]) return false;
-        return true;
+        return five == o.five;
     }
     bool operator<(const Shape &o) const {
         for (int p = 0; p < kPasses; ++p) {
             if (plan[p] != o.plan[p]) return plan[p] < o.plan[p];
             if (tile[p] != o.tile[p]) return tile[p] < o.tile[p];
         }
-        return false;
+        return five < o.five;
     }
 };
 // radix plans of a padded length: 0 the default; 1 an alternative ordering or
@@ -87,7 +90,8 @@ constexpr bool plan_exists(int N, int pv) {
 // The three-launch solve of a cube (fused.hpp): the padded lengths it is
 // built for, and the radix plan of each axis it runs (0: i3, 1: i2, 2: i1).
 // A solve takes it when its shape has these plans, so that its result is
-// bitwise that of the five passes.  The lengths are those where three
+// bitwise that of the five passes, and does not ask for the five passes'
+// tiles (Shape::five).  The lengths are those where three
 // launches measured faster, alone and several per launch, us per solve of
 // FP64 against five passes: n = 64 22.6 and 9.0 (26.9 and 13), n = 96 47.8
 // and 37.6 (51.4 and 41.6), n = 128 76.4 and 64 (89.4 and 91).  n = 72 only
@@ -103,7 +107,7 @@ constexpr bool fused_length(int N) {
 constexpr int fused_plan(int N, int axis) { return (N == 128 || N == 192 || N == 256) && axis == 2 ? 2 : 0; }
 constexpr bool fused_count(int N, bool f64, int count) { return count > 1 || !(N == 144 || (N == 192 && !f64)); }
 inline bool fused_shape(int N, const Shape &s) {
-    return fused_length(N) && s.plan[0] == fused_plan(N, 0) && s.plan[4] == fused_plan(N, 0) &&
+    return fused_length(N) && !s.five && s.plan[0] == fused_plan(N, 0) && s.plan[4] == fused_plan(N, 0) &&
            s.plan[1] == fused_plan(N, 1) && s.plan[3] == fused_plan(N, 1) && s.plan[2] == fused_plan(N, 2);
 }
 // Layout of a multiplier octant: element (|k1| = a, |k2| = b, k3 = c) of the

@@ -94,6 +94,7 @@ psp_status psp_plan_set_shape(psp_plan *p, const int *plan, const int *tile) {
         Shape s;
         psp_status rs = shape_from(p->n, plan, tile, &s);
         if (rs != PSP_OK) return rs;
+        s.five = true;
         std::lock_guard<std::mutex> lk(p->mu);
         p->shape = s;
         return PSP_OK;

@@ -1,0 +1,66 @@
+"""How many kernels a cube's solve launches: one or three where its plan starts
+from the tuning table, the five passes where a shape was set, so that a sweep of
+tiles runs the tiles it names.  Counted as the kernel nodes of a captured solve."""
+import ctypes
+
+import pytest
+
+from paper_2506_04489_amd import psp as B
+from tests.gpu_util import TILES, announce
+
+pytestmark = pytest.mark.gpu
+
+
+def _hip():
+    import torch  # noqa: F401  (loads the HIP runtime)
+    with open("/proc/self/maps") as f:
+        path = next(line.split()[-1] for line in f if "libamdhip64" in line)
+    return ctypes.CDLL(path)
+
+
+def launches(plan, rho):
+    """Kernel nodes of one captured solve of `plan` (nothing is executed)."""
+    import torch
+    hip, st = _hip(), torch.cuda.Stream()
+    u = torch.empty_like(rho)
+    s, graph, count = ctypes.c_void_p(st.cuda_stream), ctypes.c_void_p(), ctypes.c_size_t()
+    torch.cuda.synchronize()
+    assert hip.hipStreamBeginCapture(s, 2) == 0          # relaxed
+    try:
+        plan.solve_noalloc(rho, u, stream=st)
+    finally:
+        rc = hip.hipStreamEndCapture(s, ctypes.byref(graph))
+    assert rc == 0 and hip.hipGraphGetNodes(graph, None, ctypes.byref(count)) == 0
+    nodes = (ctypes.c_void_p * count.value)()
+    assert hip.hipGraphGetNodes(graph, nodes, ctypes.byref(count)) == 0
+    for node in nodes:
+        kind = ctypes.c_int(-1)
+        assert hip.hipGraphNodeGetType(ctypes.c_void_p(node), ctypes.byref(kind)) == 0 and kind.value == 0
+    assert hip.hipGraphDestroy(graph) == 0
+    return count.value
+
+
+def _noise(n, dtype):
+    import torch
+    g = torch.Generator().manual_seed(n)
+    v = torch.randn((n,) * 3, generator=g, dtype=torch.float64)
+    return v.to(torch.float64 if dtype == "f64" else torch.float32).cuda()
+
+
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("n", [4, 8, 16, 18, 24, 36, 48, 64, 128])
+def test_a_set_shape_runs_its_five_passes(n, dtype):
+    import torch
+    announce("routes n=%d %s" % (n, dtype))
+    rho = _noise(n, dtype)
+    p = B.Plan(n, 2.0 / n, 40, dtype=dtype).precompute()
+    assert launches(p, rho) == (1 if n <= 8 else 3)
+    u = p.solve(rho)
+    plan, _ = p.shape()
+    for r in (0, 1, 5, 20):
+        p.set_shape(plan, [r % c for c in TILES])
+        assert launches(p, rho) == 5
+        v = p.solve(rho)
+        torch.cuda.synchronize()
+        assert torch.equal(u, v), r
+    p.close()
