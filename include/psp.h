@@ -257,10 +257,19 @@ psp_status psp_tuning_get(int n, psp_dtype dtype, int *plan, int *tile);
  * times its four fastest candidates and the other cache policies of its pick
  * as whole solves inside that pick (the sum of the two inputs' medians over
  * `reps` solves each; a cache policy can slow its own pass and speed up the
- * next) and keeps one that is more than 0.2% faster, sets the result as the
- * plan's shape and enters it in the tuning table.  Outputs (host arrays, each may be
+ * next) and keeps one that is more than 0.2% faster.  Where a single solve of
+ * the cube can take three launches (or one; see psp_plan_set_shape), it then
+ * times whole solves of the pick in five passes against that and takes the
+ * three launches if they are more than 0.2% faster, with the fastest
+ * tiles of their radix plans for the solves that need five passes.  Sets the
+ * result as the plan's shape and enters it in the tuning table; a choice of
+ * five passes under the three launches' radix plans lasts as long as the
+ * process and the plan (psp_tuning_set cannot express it).  Everything is
+ * timed on single solves: FP32 n = 96, which takes three launches only with
+ * several solves per launch, may end with radix plans that keep its batches
+ * on five passes.  Outputs (host arrays, each may be
  * NULL): best_plan[5], best_tile[5], best_ms[5] the chosen candidate and
- * that pass's time in ms; cand_ms[5 * 63]: the time of candidate
+ * that pass's time in ms in a solve of five passes; cand_ms[5 * 63]: the time of candidate
  * (plan, tile) of pass i at cand_ms[i * 63 + plan * 21 + tile], -1 where the
  * candidate does not exist.  Allocates three n^3
  * buffers for the duration; synchronises `stream`.  PSP_ESTATE before

@@ -110,6 +110,16 @@ inline bool fused_shape(int N, const Shape &s) {
     return fused_length(N) && !s.five && s.plan[0] == fused_plan(N, 0) && s.plan[4] == fused_plan(N, 0) &&
            s.plan[1] == fused_plan(N, 1) && s.plan[3] == fused_plan(N, 1) && s.plan[2] == fused_plan(N, 2);
 }
+// The autotuner's choice between its pick for the five passes and the
+// three-launch solve, from whole solves timed the same way: three launches
+// when they are more than 0.2% faster, as in its other steps.  The five-pass
+// pick asks for its five passes where it would otherwise run in three launches.
+inline Shape route_pick(int N, Shape five, float five_ms, Shape three, float three_ms) {
+    five.five = three.five = false;
+    if (three_ms < 0.998f * five_ms) return three;
+    five.five = fused_shape(N, five);
+    return five;
+}
 // Layout of a multiplier octant: element (|k1| = a, |k2| = b, k3 = c) of the
 // (n2+1) x P x (n1+1) doubles.  Rows ([b][c][a], for cubes of a fused
 // length): the fused pass reads all a of one (b, c).  Blocked

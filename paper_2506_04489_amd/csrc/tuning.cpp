@@ -1,6 +1,7 @@
 // tuning.cpp - launch shapes of the passes: per-plan setting, the
 // process-wide tuning table, and the autotuner that measures every
-// (radix plan, tile) candidate of every pass with HIP events.
+// (radix plan, tile) candidate of every pass with HIP events, and the
+// three-launch solve of a cube against its pick.
 #include <algorithm>
 #include <cfloat>
 #include <map>
@@ -191,6 +192,7 @@ psp_status psp_autotune(psp_plan *p, int reps, void *stream, int *best_plan, int
         // both go into its median
         for (size_t r = 0; r < 2 * rounds && out == PSP_OK; ++r) {
             Shape s;
+            s.five = true;      // the warm-up too
             for (int i = 0; i < kPasses; ++i) {
                 const auto &c = cand[i][(r / 2) % cand[i].size()];
                 s.plan[i] = c.first;
@@ -237,6 +239,7 @@ psp_status psp_autotune(psp_plan *p, int reps, void *stream, int *best_plan, int
                 if (best[i][c] < 0.99f * best[i][0] && best[i][c] < best[i][pick[i]]) pick[i] = c;
         auto shape_of = [&](const std::vector<size_t> &pk) {
             Shape s;
+            s.five = true;
             for (int i = 0; i < kPasses; ++i) {
                 s.plan[i] = cand[i][pk[i]].first;
                 s.tile[i] = cand[i][pk[i]].second;
@@ -302,36 +305,46 @@ psp_status psp_autotune(psp_plan *p, int reps, void *stream, int *best_plan, int
                 }
             }
         }
-        // lengths with a three-launch solve: its plans, if it beats the five
-        // passes of the pick (events around the whole solve; per-pass events
-        // would make it run as five passes)
-        if (out == PSP_OK && fused_length(2 * n) && p->chunk_tiles <= 0 && p->i1_group <= 0) {
+        // lengths whose single solves take three launches: whole solves of the
+        // pick in five passes and of the three launches (with the fastest
+        // tiles of their plans, for the solves that need five passes), both
+        // with an event before the first launch and one after the last
+        Shape chosen = shape_of(pick);
+        chosen.five = false;
+        if (out == PSP_OK && fused_length(2 * n) && fused_count(2 * n, !f32, 1) && p->chunk_tiles <= 0 &&
+            p->i1_group <= 0) {
             std::vector<size_t> fp = pick;
             for (int i = 0; i < kPasses; ++i) {
                 const int pl = fused_plan(2 * n, i == 2 ? 2 : i == 0 || i == 4 ? 0 : 1);
+                if (cand[i][pick[i]].first == pl) continue;
                 size_t b = cand[i].size();
                 for (size_t c = 0; c < cand[i].size(); ++c)
                     if (cand[i][c].first == pl && (b == cand[i].size() || best[i][c] < best[i][b])) b = c;
                 fp[i] = b;
             }
-            float score = 0;
-            for (int in = 0; in < 2 && out == PSP_OK; ++in) {
-                SolveArgs a = solve_args(p, *w, in ? rho_b : rho, u);
-                a.shape = shape_of(fp);
+            Shape side[2] = {shape_of(pick), shape_of(fp)};
+            side[1].five = false;
+            float ms[2] = {0, 0};
+            for (int k = 0; k < 4 && out == PSP_OK; ++k) {     // each side on each input
+                SolveArgs a = solve_args(p, *w, k / 2 ? rho_b : rho, u);
+                a.shape = side[k % 2];
                 std::vector<float> t;
                 for (int rep = 0; rep <= reps && out == PSP_OK; ++rep) {   // the first is a warm-up
-                    float ms = 0;
+                    float x = 0;
                     if ((e = hipEventRecord(ev[0], st)) != hipSuccess || (e = launch_solve(a, st)) != hipSuccess ||
                         (e = hipEventRecord(ev[1], st)) != hipSuccess || (e = hipEventSynchronize(ev[1])) != hipSuccess ||
-                        (e = hipEventElapsedTime(&ms, ev[0], ev[1])) != hipSuccess)
+                        (e = hipEventElapsedTime(&x, ev[0], ev[1])) != hipSuccess)
                         out = hip_fail(e, "autotune solve");
-                    if (rep > 0) t.push_back(ms);
+                    if (rep > 0) t.push_back(x);
                 }
                 if (out != PSP_OK) break;
                 std::sort(t.begin(), t.end());
-                score += t[t.size() / 2];
+                ms[k % 2] += t[t.size() / 2];
             }
-            if (out == PSP_OK && score < cur) pick = fp;
+            if (out == PSP_OK) {
+                chosen = route_pick(2 * n, side[0], ms[0], side[1], ms[1]);
+                if (!chosen.five && fused_shape(2 * n, chosen)) pick = fp;
+            }
         }
         if (out == PSP_OK && (e = hipStreamSynchronize(st)) != hipSuccess) out = hip_fail(e, "autotune");
         for (auto x : ev)
@@ -340,7 +353,6 @@ psp_status psp_autotune(psp_plan *p, int reps, void *stream, int *best_plan, int
         (void)hipFree(rho_b);
         (void)hipFree(u);
         if (out != PSP_OK) return out;
-        const Shape chosen = shape_of(pick);
         if (best_ms)
             for (int i = 0; i < kPasses; ++i) best_ms[i] = best[i][pick[i]];
         {

@@ -64,3 +64,26 @@ def test_a_set_shape_runs_its_five_passes(n, dtype):
         torch.cuda.synchronize()
         assert torch.equal(u, v), r
     p.close()
+
+
+@pytest.mark.parametrize("n,dtype", [(8, "f64"), (48, "f64"), (64, "f32"), (72, "f64"), (96, "f32")])
+def test_the_autotuned_route_is_the_one_solves_take(n, dtype):
+    import torch
+    announce("autotuned route n=%d %s" % (n, dtype))
+    old = B.tuning_get(n, dtype)
+    rho = _noise(n, dtype)
+    try:
+        p = B.Plan(n, 2.0 / n, 40, dtype=dtype).precompute()
+        p.autotune(reps=1)
+        count = launches(p, rho)
+        # one solve of these lengths takes five passes whatever the plans
+        assert count == 5 if n in (72, 96) else count in (1, 3, 5)
+        q = B.Plan(n, 2.0 / n, 40, dtype=dtype).precompute()    # from the table
+        assert q.shape() == p.shape() and launches(q, rho) == count
+        u = p.solve(rho)
+        p.profile_enable(1)                                     # five passes
+        five = p.solve(rho)
+        torch.cuda.synchronize()
+        assert torch.equal(u, five)
+    finally:
+        B.tuning_set(n, dtype, *old)
