@@ -137,7 +137,17 @@ hipError_t launch_batch_image(const std::vector<BatchMember> &m, const BatchImag
         size_t j = i;
         const BatchMember &b = m[g[i]];
         while (j < g.size() && m[g[j]].n == b.n && m[g[j]].shape == b.shape) ++j;
-        hipError_t e = launch_group(b.n, f32, b.shape, (const Job *)(dev_base + img.group_off) + i, (int)(j - i),
+        Shape shape = b.shape;
+        if (2 * b.n <= SINGLE_MAX && j - i > 1) {
+            std::vector<const void *> rho;
+            std::vector<void *> u;
+            for (size_t k = i; k < j; ++k) {
+                rho.push_back(m[g[k]].job.rho);
+                u.push_back(m[g[k]].job.u);
+            }
+            if (feeds_another(rho, u, (size_t)b.n * b.n * b.n * (f32 ? 4 : 8))) shape.five = true;
+        }
+        hipError_t e = launch_group(b.n, f32, shape, (const Job *)(dev_base + img.group_off) + i, (int)(j - i),
                                     b.tw64, st);
         if (e != hipSuccess) return e;
         i = j;

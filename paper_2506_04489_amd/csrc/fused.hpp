@@ -77,9 +77,6 @@ template <int N, int PV, bool INV> struct SubSeq {
     }
 };
 
-// the largest padded length of the one-workgroup solve (single.hpp says why)
-constexpr int SINGLE_MAX = 16;
-
 // Tile of the fused kernels: J columns per workgroup of F1 and F3, KU bins
 // per thread and round of F3, NB blocks per workgroup of F2.
 template <typename T, int N> struct FusedCfg {

@@ -2,6 +2,11 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+#include <cstdint>
+#include <utility>
+#include <vector>
+
 namespace psp {
 
 // One solve's device pointers as the pass kernels see them.
@@ -104,6 +109,8 @@ constexpr bool fused_length(int N) {
     return N == 8 || N == 12 || N == 16 || N == 24 || N == 32 || N == 36 || N == 48 || N == 64 || N == 72 ||
            N == 96 || N == 108 || N == 128 || N == 144 || N == 192 || N == 256;
 }
+// the largest padded length of the one-workgroup solve (single.hpp says why)
+constexpr int SINGLE_MAX = 16;
 constexpr int fused_plan(int N, int axis) { return (N == 128 || N == 192 || N == 256) && axis == 2 ? 2 : 0; }
 constexpr bool fused_count(int N, bool f64, int count) { return count > 1 || !(N == 144 || (N == 192 && !f64)); }
 inline bool fused_shape(int N, const Shape &s) {
@@ -211,6 +218,23 @@ struct SolveArgs {
 };
 
 hipError_t launch_solve(const SolveArgs &s, hipStream_t st);
+
+// Whether a u (of `bytes` bytes) overlaps the rho of another solve of a
+// group.  One workgroup per solve (single.hpp) then must not run the group:
+// it may write that u before the other solve's workgroup reads its rho.  With
+// several launches every rho is read before any u is written.
+inline bool feeds_another(const std::vector<const void *> &rho, const std::vector<void *> &u, size_t bytes) {
+    std::vector<std::pair<uintptr_t, size_t>> at;
+    for (size_t i = 0; i < rho.size(); ++i) at.push_back({(uintptr_t)rho[i], i});
+    std::sort(at.begin(), at.end());
+    for (size_t i = 0; i < u.size(); ++i) {
+        const uintptr_t x = (uintptr_t)u[i], lo = x < bytes ? 0 : x - bytes + 1;
+        for (auto it = std::lower_bound(at.begin(), at.end(), std::make_pair(lo, (size_t)0));
+             it != at.end() && it->first < x + bytes; ++it)
+            if (it->second != i) return true;
+    }
+    return false;
+}
 
 // `count` solves of the same n and tier in one launch per pass; `table_dev`
 // is a device array of `count` jobs, each with a workspace of one chunk

@@ -4,8 +4,11 @@
 // them.  Bound by launches and latency: one launch in place of three (FP64,
 // us per solve in a row: n = 4 13.5 -> 4.6, n = 8 13.6 -> 6.8; five launches
 // took 20).  At n = 12 the i1 columns take two rounds and one CU needs 16.8
-// us, longer than the three launches' 12.6.  Each transform has the plan, twiddles and order
-// of operations of its pass kernel, so results are bitwise theirs.
+// us, longer than the three launches' 12.6.  Each transform has the plan,
+// twiddles and order of operations of its pass kernel, so results are bitwise
+// theirs.  A batch whose outputs overlap inputs of other members of the same
+// size takes the five passes (feeds_another): workgroups of one launch have
+// no order.
 #pragma once
 #include "passes.hpp"
 

@@ -1,5 +1,6 @@
-// Which route a launch shape takes, and the autotuner's choice between five
-// passes and three launches (host functions of csrc/kernels.h).
+// Which route a launch shape takes, the autotuner's choice between five
+// passes and three launches, and which groups one launch must not run (host
+// functions of csrc/kernels.h).
 #include <cstdio>
 
 #include "../../paper_2506_04489_amd/csrc/kernels.h"
@@ -47,6 +48,17 @@ int main() {
     const Shape kept = route_pick(128, other, 10.0f, shape(128, 0, true), 12.0f);
     EXPECT(kept == other && !kept.five && !fused_shape(128, kept));
     EXPECT(!fused_shape(512, Shape{}) && !fused_shape(216, Shape{}));
+    // a u over the rho of another solve, wholly or by one byte, and not over its own
+    char b[4096];
+    const size_t w = 512;
+    EXPECT(!feeds_another({b, b + w}, {b + 2 * w, b + 3 * w}, w));
+    EXPECT(feeds_another({b, b + w}, {b + w, b}, w));
+    EXPECT(feeds_another({b, b + w}, {b + 2 * w, b + w - 1}, w) && feeds_another({b, b + 2 * w}, {b + 4 * w, b + w - 1}, w));
+    EXPECT(!feeds_another({b, b + w}, {b + 4 * w, b + 2 * w}, w) && !feeds_another({b + w, b + 3 * w}, {b, b + 2 * w}, w));
+    EXPECT(!feeds_another({b, b + 4 * w}, {b + 8, b + 4 * w + 8}, w));
+    EXPECT(feeds_another({b, b}, {b + 8, b + 4 * w}, w));
+    EXPECT(!feeds_another({(void *)8, (void *)4096}, {(void *)1024, (void *)2048}, w));
+    EXPECT(feeds_another({(void *)8, (void *)4096}, {(void *)1024, (void *)16}, w));
     std::printf("%d failures\n", failures);
     return failures != 0;
 }

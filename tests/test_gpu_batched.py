@@ -177,3 +177,30 @@ def test_persistent_batch_covers_every_size_and_large_members(mode):
             assert torch.equal(u, alone), p.n
     finally:
         B.set_batch_mode("grouped")
+
+
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("n", [4, 8, 16, 24])
+def test_outputs_over_other_members_inputs(n, dtype):
+    """A batch of one size whose outputs go over the inputs of other members (in
+    a ring, and over the ends of two) solves every input as it was."""
+    import torch
+    td = torch.float64 if dtype == "f64" else torch.float32
+    p = B.Plan(n, 2.0 / n, 40, dtype=dtype).precompute()
+    g = torch.Generator().manual_seed(n)
+    size, k = n ** 3, 24
+    base = torch.randn((k + 2) * size, generator=g, dtype=torch.float64).to(td).cuda()
+    for ring in (True, False):
+        buf = base.clone()
+        rhos = [buf[i * size:(i + 1) * size].view(n, n, n) for i in range(k)]
+        outs, want = [], []
+        for i in range(k):
+            a = (i + 1) % k * size if ring else i * size + size + size // 2
+            over = ring or i % 3 == 0                       # these do not overlap each other
+            outs.append(buf[a:a + size].view(n, n, n) if over else torch.empty_like(rhos[i]))
+            want.append(p.solve(rhos[i].clone()))
+        torch.cuda.synchronize()
+        B.solve_batched([p] * k, rhos, outs)
+        torch.cuda.synchronize()
+        for i in range(k):
+            assert torch.equal(outs[i], want[i]), (ring, i)
