@@ -80,14 +80,14 @@ template <int N, int PV, bool INV> struct SubSeq {
 // Tile of the fused kernels: J columns per workgroup of F1 and F3, KU bins
 // per thread and round of F3, NB blocks per workgroup of F2.
 template <typename T, int N> struct FusedCfg {
-    static constexpr int J = N == 36 ? 2 : N == 108 ? 6 : N == 256 ? 8 : N == 192 ? (sizeof(T) == 8 ? 12 : 8) : 4;
-    static constexpr int KU = N == 256 ? 1 : N == 144 || N == 192 ? 2 : 3;
+    static constexpr int J = N == 36 ? 2 : N == 108 ? 6 : N == 144 ? 12 : N == 256 ? 8 : N == 192 ? (sizeof(T) == 8 ? 12 : 8) : 4;
+    static constexpr int KU = N == 144 || N == 256 ? 1 : N == 192 ? 2 : 3;
     // J of F1 and of F3, KU of F3, with several solves per launch: there are
     // workgroups enough for wider rows of A (n = 64 7.34 -> 7.16 us per solve,
     // FP32 4.69 -> 4.38; n = 128 FP32 40.1 -> 37.9; n = 72 15.7 -> 15.0)
-    static constexpr int J1M = N == 128 ? 8 : N == 256 && sizeof(T) == 4 ? 16 : N == 144 ? 12 : J;
-    static constexpr int J3M = N == 128 ? 8 : N == 192 && sizeof(T) == 8 ? 4 : N == 144 ? 12 : J;
-    static constexpr int KUM = N == 128 ? 2 : N == 192 && sizeof(T) == 8 ? 3 : N == 144 ? 1 : KU;
+    static constexpr int J1M = N == 128 ? 8 : N == 256 && sizeof(T) == 4 ? 16 : J;
+    static constexpr int J3M = N == 128 ? 8 : N == 192 && sizeof(T) == 8 ? 4 : J;
+    static constexpr int KUM = N == 128 ? 2 : N == 192 && sizeof(T) == 8 ? 3 : KU;
     static constexpr int NB = N <= 32 ? 4 : N == 36 ? 2 : 1;
     // the 17 MB of A of one solve at n = 64 FP64 written and read past the
     // caches: 26.7 -> 24.2 us for the three launches (other sizes and several
@@ -632,10 +632,13 @@ template <typename T, int N> hipError_t fused_solve(const Job &one, const Job *t
             hipLaunchKernelGGL((k_f_inv<T, N, PZ, PY, J3, KU, CP>), dim3(xcd_blocks(n * F3::GROUPS), count),
                                dim3(F3::THREADS), 0, st, jr, tw);
         };
+        // (lengths whose single solves take five passes have no kernels for them)
         if (count > 1)
             launch(Const<1>{});
-        else
+        else if constexpr (fused_count(N, sizeof(T) == 8, 1))
             launch(Const<0>{});
+        else
+            return hipErrorInvalidValue;
     }
     return hipGetLastError();
 }

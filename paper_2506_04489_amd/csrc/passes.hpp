@@ -100,8 +100,6 @@ template <int W> struct IdxInter {   // (position, column) -> position*W + colum
 struct IdxLine {                     // column-major, one padding slot per 8 positions
     int base;
     __device__ __forceinline__ int operator()(int pos) const { return base + pos + (pos >> 3); }
-    __device__ __forceinline__ int scalar(int pos) const { return base + pos + (pos >> 3); }
-    template <int> static constexpr bool blocked() { return false; }
 };
 
 // Plain accesses to the solve's buffers, all global memory, made through
