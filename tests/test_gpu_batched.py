@@ -204,3 +204,32 @@ def test_outputs_over_other_members_inputs(n, dtype):
         torch.cuda.synchronize()
         for i in range(k):
             assert torch.equal(outs[i], want[i]), (ring, i)
+
+
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("mode", ["persistent", "flat"])
+def test_persistent_kernels_at_every_length_and_plan(mode, dtype):
+    """The persistent (flat) kernels hold radix plans 0 and 1; tuned members with
+    plan 2 take the grouped launches instead.  Every length they are built for
+    with plan 0, and 2n = 128 and 256 with plan 1, against five passes."""
+    import torch
+    td = torch.float64 if dtype == "f64" else torch.float32
+    members = [(n, 0) for n in (4, 6, 8, 12, 16, 24, 32, 48, 64, 96, 128)] + [(64, 1), (128, 1)]
+    ps, rhos = [], []
+    for i, (n, plan) in enumerate(members):
+        ps.append(B.Plan(n, 2.0 / n, 40, dtype=dtype).precompute().set_shape([plan] * 5, [0] * 5))
+        g = torch.Generator().manual_seed(61 + i)
+        rhos.append(torch.randn((n,) * 3, generator=g, dtype=torch.float64).to(td).cuda())
+    us = [torch.empty_like(r) for r in rhos]
+    B.set_batch_mode(mode)
+    try:
+        B.solve_batched(ps, rhos, us)
+        torch.cuda.synchronize()
+    finally:
+        B.set_batch_mode("grouped")
+    for (n, plan), p, r, u in zip(members, ps, rhos, us):
+        p.profile_enable(1)
+        five = p.solve(r)
+        torch.cuda.synchronize()
+        assert p.profile_read()[0] == 1
+        assert torch.equal(u, five), (n, plan)
