@@ -176,8 +176,10 @@ psp_status psp_solve_padded_debug(const psp_plan *p, const void *rho_dev, void *
  * allocated afterwards (plans, batches, graphs, the serving loop) places its
  * two intermediates 64 KB into their allocations, between 64 KB bands filled
  * with the byte 0xA5.  psp_plan_check_guards synchronises the device and sets
- * *intact = 1 if every band of the plan's workspaces still holds the pattern
- * (0 otherwise; workspaces allocated without guards are skipped). */
+ * *intact = 1 if every band of the plan's workspaces, and of those that
+ * psp_solve_batched holds for solves of its point counts and tier on its
+ * device, still holds the pattern (0 otherwise; workspaces allocated without
+ * guards are skipped). */
 psp_status psp_debug_guards(int enable);
 psp_status psp_plan_check_guards(psp_plan *p, int *intact);
 

@@ -643,16 +643,21 @@ psp_status psp_debug_guards(int enable) {
 psp_status psp_plan_check_guards(psp_plan *p, int *intact) {
     return guarded([&]() -> psp_status {
         if (!p || !intact) return fail(PSP_EINVAL, "NULL argument");
-        std::lock_guard<std::mutex> lk(p->mu);
         PSP_HIP(hipDeviceSynchronize(), "hipDeviceSynchronize");
         bool all = true;
-        for (auto &kv : p->ws) {
-            bool ok = true;
-            psp_status st = check_guards(kv.second, &ok);
-            if (st != PSP_OK) return st;
-            all = all && ok;
+        {
+            std::lock_guard<std::mutex> lk(p->mu);
+            for (auto &kv : p->ws) {
+                bool ok = true;
+                psp_status st = check_guards(kv.second, &ok);
+                if (st != PSP_OK) return st;
+                all = all && ok;
+            }
         }
-        *intact = all ? 1 : 0;
+        bool batches = true;
+        psp_status st = check_batch_guards(p, &batches);
+        if (st != PSP_OK) return st;
+        *intact = all && batches ? 1 : 0;
         return PSP_OK;
     });
 }

@@ -254,6 +254,31 @@ static psp_status batch_workspaces(StreamBatch &B, const std::vector<int> &ns, b
     return PSP_OK;
 }
 
+psp_status check_batch_guards(const psp_plan *p, bool *intact) {
+    const bool f32 = p->dtype == PSP_F32;
+    std::lock_guard<std::mutex> lk(g_batch_mu);
+    *intact = true;
+    std::vector<const Workspace *> all;
+    for (const auto &kv : g_batch) {
+        if (kv.first.first != p->device) continue;
+        if (p->grid) {
+            const auto it = kv.second.grid_ws.find({std::vector<int>{p->ns[0], p->ns[1], p->ns[2]}, f32});
+            if (it != kv.second.grid_ws.end()) all.push_back(&it->second);
+        } else {
+            const auto it = kv.second.ws.find({p->n, f32});
+            if (it == kv.second.ws.end()) continue;
+            for (const Workspace &w : it->second) all.push_back(&w);
+        }
+    }
+    for (const Workspace *w : all) {
+        bool ok = true;
+        const psp_status rs = check_guards(*w, &ok);
+        if (rs != PSP_OK) return rs;
+        *intact = *intact && ok;
+    }
+    return PSP_OK;
+}
+
 // serving: jobs whose workspaces the caller owns (one chunk of all tiles)
 hipError_t launch_batch(int count, const SolveArgs *args, hipStream_t st) {
     if (count <= 0) return hipSuccess;

@@ -79,6 +79,9 @@ constexpr unsigned char kGuardByte = 0xA5;
 bool guards_enabled();
 // the guard bands of w are intact (reads them back; synchronous)
 psp_status check_guards(const Workspace &w, bool *intact);
+// the same of every batch workspace for solves like p's (its device, point
+// counts and tier), on any stream
+psp_status check_batch_guards(const psp_plan *p, bool *intact);
 
 inline int pitch_for(int n) { return ((n + 1 + 15) / 16) * 16; }
 // k3 columns of the H2-H4 chunk buffer for a chunk of `chunk_tiles` tiles

@@ -332,8 +332,9 @@ class Plan:
         return self
 
     def guards_intact(self) -> bool:
-        """psp_plan_check_guards: the guard bands of this plan's workspaces
-        (allocated while psp_debug_guards was on) are untouched."""
+        """psp_plan_check_guards: the guard bands of this plan's workspaces and
+        of the batch workspaces of its size and tier (those allocated while
+        psp_debug_guards was on) are untouched."""
         ok = ctypes.c_int()
         _check(lib().psp_plan_check_guards(self._h, ctypes.byref(ok)))
         return bool(ok.value)

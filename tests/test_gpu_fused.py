@@ -58,3 +58,33 @@ def test_fused_equals_the_five_passes_bitwise(n, dtype):
         p.close()
     finally:
         B.debug_guards(False)
+
+
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("n", FUSED)
+def test_batched_fused_solves_stay_inside_their_workspaces(n, dtype):
+    """The tiles that several solves per launch take, in guarded workspaces: a
+    stream of its own has a pool of its own, allocated by this batch."""
+    import ctypes
+
+    import torch
+    with open("/proc/self/maps") as f:
+        hip = ctypes.CDLL(next(line.split()[-1] for line in f if "libamdhip64" in line))
+    st = ctypes.c_void_p()
+    rhos = [_noise(n, dtype, 900 + i) for i in range(3)]
+    us = [torch.empty_like(r) for r in rhos]
+    p = B.Plan(n, 2.0 / n, 40, dtype=dtype).precompute()
+    torch.cuda.synchronize()
+    assert hip.hipStreamCreate(ctypes.byref(st)) == 0
+    B.debug_guards(True)
+    try:
+        B.solve_batched([p] * 3, rhos, us, stream=st.value)
+        torch.cuda.synchronize()
+        assert p.guards_intact()
+    finally:
+        B.debug_guards(False)
+    for r, u in zip(rhos, us):
+        want = p.solve(r)
+        torch.cuda.synchronize()
+        assert torch.equal(u, want)
+    p.close()
