@@ -6,6 +6,7 @@
 // time, the launches 2.5 us each (n = 48 FP32: 25.2 -> 16.8 us per
 // replay).
 #include <algorithm>
+#include <mutex>
 #include <vector>
 
 #include "host_common.hpp"
@@ -15,6 +16,7 @@ struct psp_graph {
     hipGraphExec_t exec = nullptr;
     std::vector<psp::Workspace> ws;
     psp::SolveArgs solve;             // a single solve (exec is null)
+    std::mutex mu;                    // its launches follow one another on their stream
     unsigned char *table = nullptr;   // device batch image
     int device = -1;
 };
@@ -182,6 +184,9 @@ psp_status psp_graph_launch(psp_graph *g, void *stream) {
             if (e != hipSuccess) return hip_fail(e, "hipGraphLaunch");
             return PSP_OK;
         }
+        // two threads that replay one record on one stream must not mix its
+        // launches: the passes update the workspace in place
+        std::lock_guard<std::mutex> lk(g->mu);
         int dev = -1;
         hipError_t e = hipGetDevice(&dev);
         if (e == hipSuccess && dev != g->device) e = hipSetDevice(g->device);

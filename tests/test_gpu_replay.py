@@ -33,3 +33,43 @@ def test_replays_follow_their_stream(n):
         torch.cuda.synchronize()
         assert torch.equal(o, want), k
     rec.close()
+
+
+@pytest.mark.parametrize("n", [48, 96, 108])
+def test_threads_replay_one_record_on_one_stream(n):
+    """Replays of one record by several threads on one stream follow one another
+    whole: their launches share a workspace that the passes update in place."""
+    import threading
+
+    import torch
+    announce("replay by threads %d" % n)
+    g = torch.Generator().manual_seed(5)
+    rho = torch.randn((n,) * 3, generator=g, dtype=torch.float64).cuda()
+    p = B.Plan(n, 2.0 / n, 40).precompute()
+    want = p.solve(rho)
+    u = torch.empty_like(rho)
+    rec = B.Graph.capture(p, rho, u)
+    st = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    for _ in range(20):
+        u.zero_()
+        torch.cuda.synchronize()
+        go, errors = threading.Barrier(4), []
+
+        def replay():
+            try:
+                go.wait(timeout=30)
+                for _ in range(8):
+                    rec.launch(stream=st)
+            except Exception as e:          # reported below, in the test's thread
+                errors.append(e)
+
+        threads = [threading.Thread(target=replay) for _ in range(4)]
+        for t in threads:
+            t.start()
+        for t in threads:
+            t.join()
+        st.synchronize()
+        assert not errors
+        assert torch.equal(u, want)
+    rec.close()
