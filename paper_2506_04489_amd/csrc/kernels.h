@@ -46,6 +46,10 @@ constexpr int kPasses = 5;
 constexpr int kTileChoices[kPasses] = {8, 14, 21, 14, 8};
 constexpr int kMaxTiles = 21;     // the largest of kTileChoices
 constexpr int kMaxPlans = 3;      // radix plans 0..2
+// the H2-H4 tile with all threads per column in place of half of them
+constexpr int full_threads(int tile) {
+    return tile % 7 == 3 ? tile - 3 : tile % 7 == 4 ? tile - 2 : tile % 7 == 6 ? tile - 1 : tile;
+}
 // points along i1, i2, i3 (the slowest to the contiguous axis of rho)
 struct Dims {
     int n1, n2, n3;

@@ -714,8 +714,17 @@ hipError_t passes_impl(const Job &one, const Job *table, int count, int P, int c
         });
     };
     auto h3 = [&](const JobRef &jr, const Chunk &ck) {
+        // Half the threads per column pay where the pass fills the chip.  A
+        // grid's pass (mask) has the tile of the cube of its i1 length and may
+        // have far fewer columns: below three workgroups per CU it runs all
+        // threads (whole solves, us: FP64 192x8x216 38.5 -> 35.9, 192x54x36
+        // 40.1 -> 39.1, 216x54x36 46.3 -> 42.1, FP32 256x8x48 25.1 -> 21.6; at
+        // 6100 workgroups 192x108x216 takes 198.2 with half and 208.8 with
+        // all).  N = 768 is faster with half at every size (384x64x48 FP64
+        // 79.9 against 84.1).
+        const bool few = mask != 0x1f && N < 768 && 2L * (ck.n2 + 1) * ck.ntile < 3 * 256;
         with_plan<N>(sh.plan[2], [&](auto pv) {
-            with_h3_tile<T>(sh.tile[2], [&](auto w, auto cp) {
+            with_h3_tile<T>(few ? full_threads(sh.tile[2]) : sh.tile[2], [&](auto w, auto cp) {
                 constexpr int PV = decltype(pv)::value, W = decltype(w)::W;
                 constexpr int XC = decltype(w)::XC;
                 constexpr bool HF = decltype(w)::HF;

@@ -48,6 +48,11 @@ int main() {
     const Shape kept = route_pick(128, other, 10.0f, shape(128, 0, true), 12.0f);
     EXPECT(kept == other && !kept.five && !fused_shape(128, kept));
     EXPECT(!fused_shape(512, Shape{}) && !fused_shape(216, Shape{}));
+    // tiles with half the threads per column and their forms with all of them
+    for (int c = 0; c < 3; ++c) {
+        const int full[7] = {0, 1, 2, 0, 2, 5, 5};
+        for (int t = 0; t < 7; ++t) EXPECT(full_threads(7 * c + t) == 7 * c + full[t]);
+    }
     // a u over the rho of another solve, wholly or by one byte, and not over its own
     char b[4096];
     const size_t w = 512;

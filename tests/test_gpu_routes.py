@@ -20,6 +20,11 @@ def _hip():
 
 def launches(plan, rho):
     """Kernel nodes of one captured solve of `plan` (nothing is executed)."""
+    return len(block_sizes(plan, rho))
+
+
+def block_sizes(plan, rho):
+    """Threads per workgroup of the kernels of a captured solve, in order."""
     import torch
     hip, st = _hip(), torch.cuda.Stream()
     u = torch.empty_like(rho)
@@ -33,11 +38,14 @@ def launches(plan, rho):
     assert rc == 0 and hip.hipGraphGetNodes(graph, None, ctypes.byref(count)) == 0
     nodes = (ctypes.c_void_p * count.value)()
     assert hip.hipGraphGetNodes(graph, nodes, ctypes.byref(count)) == 0
+    sizes = []
     for node in nodes:
-        kind = ctypes.c_int(-1)
+        kind, params = ctypes.c_int(-1), (ctypes.c_uint32 * 64)()       # blockDim comes first
         assert hip.hipGraphNodeGetType(ctypes.c_void_p(node), ctypes.byref(kind)) == 0 and kind.value == 0
+        assert hip.hipGraphKernelNodeGetParams(ctypes.c_void_p(node), params) == 0
+        sizes.append(params[0])
     assert hip.hipGraphDestroy(graph) == 0
-    return count.value
+    return sizes
 
 
 def _noise(n, dtype):
@@ -87,3 +95,27 @@ def test_the_autotuned_route_is_the_one_solves_take(n, dtype):
         assert torch.equal(u, five)
     finally:
         B.tuning_set(n, dtype, *old)
+
+
+@pytest.mark.parametrize("ns,dtype,few", [((192, 8, 48), "f64", True), ((192, 54, 36), "f64", True),
+                                          ((192, 128, 48), "f64", False), ((256, 8, 48), "f32", True),
+                                          ((256, 96, 96), "f32", False)])
+def test_a_grids_i1_pass_has_all_threads_where_columns_are_few(ns, dtype, few):
+    import torch
+    announce("i1 pass of %s %s" % (ns, dtype))
+    n, (plan, tile) = ns[0], B.tuning_get(ns[0], dtype)
+    g = torch.Generator().manual_seed(1)
+    rho = torch.randn(ns, generator=g, dtype=torch.float64).cuda()
+    rho = rho.to(torch.float64 if dtype == "f64" else torch.float32)
+    sizes, us = {}, {}
+    try:
+        for t in (2, 4):                # half-size exchanges, all threads and half of them
+            B.tuning_set(n, dtype, plan, [t if q == 2 else x for q, x in enumerate(tile)])
+            p = B.Plan(ns, tuple(2.0 / m for m in ns), 40, dtype=dtype).precompute()
+            sizes[t], us[t] = block_sizes(p, rho), p.solve(rho)
+            torch.cuda.synchronize()
+            p.close()
+    finally:
+        B.tuning_set(n, dtype, plan, tile)
+    assert (sizes[2] == sizes[4]) == few, sizes
+    assert torch.equal(us[2], us[4])
