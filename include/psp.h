@@ -288,9 +288,9 @@ psp_status psp_plan_spectrum_bytes(const psp_plan *p, size_t *bytes);
 /* Per-pass device timing.  psp_profile_enable makes the next `max_solves`
  * psp_solve calls of this plan record 6 HIP events on their own stream:
  * before each of the 5 passes (forward i3, forward i2, fused i1 with the
- * multiply, inverse i2, inverse i3) and after the last (a cube with n <= 64,
- * n = 96 or n = 128, whose solve otherwise takes one or three launches with
- * the same result, runs as five passes while it is profiled).
+ * multiply, inverse i2, inverse i3) and after the last (a cube whose solve
+ * otherwise takes one launch, n <= 8, or three, n <= 64, n = 128 and in FP64
+ * n = 96, with the same result, runs as five passes while it is profiled).
  * psp_profile_read
  * waits for them and returns the number of recorded solves and the average
  * milliseconds of each pass (pass_ms[0..4]) and of the whole solve
@@ -309,14 +309,15 @@ psp_status psp_device_peaks(void *buf_a, void *buf_b, size_t bytes, void *stream
 
 void psp_plan_destroy(psp_plan *p);
 
-/* ---- captured solves (hipGraph) -------------------------------------------
+/* ---- recorded solves and batches ------------------------------------------
  * psp_graph_capture records one solve of (plan, rho_dev, u_dev) with its own
  * workspace; psp_graph_launch replays it on `stream` (one host call for all
  * passes, made as kernel launches: a HIP graph of so short a chain costs more
  * host time).  psp_graph_capture_batched records a batch as a HIP graph
  * (as psp_solve_batched; the graph owns the workspaces and the device
- * job table).  Replays of one graph must not overlap each other; the graph
- * keeps pointers to rho/u and to the plans' spectra, which must outlive it.
+ * job table).  Replays of one record must not overlap each other on the
+ * device (those of a recorded solve on one stream do not, from several
+ * threads either); it keeps pointers to rho/u and to the plans' spectra, which must outlive it.
  * Capture synchronises `stream`. */
 typedef struct psp_graph psp_graph;
 psp_status psp_graph_capture(const psp_plan *p, const void *rho_dev, void *u_dev, void *stream, psp_graph **out);

@@ -1,5 +1,6 @@
 // batched.hip - many independent solves on one stream.  By default solves
-// are grouped by (n, shape) with one launch per pass per group.  In the
+// are grouped by (n, shape) with one launch per pass per group (three or one
+// where the shape has such a solve).  In the
 // persistent batch mode, solves with padded length 2n <= 256 run through the
 // persistent pass kernels instead (one launch per pass for all of them, work
 // items from atomic counters) and only larger ones (and those with a radix-16
@@ -26,10 +27,13 @@ static size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 // batch mode (psp_set_batch_mode): 0 grouped launches, 1 persistent kernels
 // for 2n <= 256, 2 the same kernels with one workgroup per item.  Measured on
-// MI355X for the 64-mixture batch (n = 32..128, FP64): grouped 29.9k
-// solves/s, flat 25.6k, persistent 19.0k, one solve at a time 21.9k (each
-// persistent workgroup runs its items one after another and exposes every
-// item's load latency); so grouped launches are the default.
+// MI355X for the 64-mixture batch (n = 32..128), solves/s in FP64 and FP32:
+// grouped 38.0k and 66.7k, flat 38.6k and 65.9k, persistent 33.1k and 49.1k,
+// one solve at a time 26.1k and 34.7k.  In the other two modes only n = 32 and
+// 48 run the persistent kernels here: the tuned larger sizes have a radix-16
+// plan and take the grouped launches.  A persistent workgroup runs its items
+// one after another and exposes every item's load latency.  Grouped launches
+// are the default; flat ones differ from them by 1-2% either way here.
 static std::atomic<int> g_batch_mode{0};
 static bool persistent_enabled() { return g_batch_mode.load() != 0; }
 

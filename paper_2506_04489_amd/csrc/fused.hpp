@@ -17,13 +17,10 @@
 // real arrays of n^3 values.  Every butterfly has the inputs, twiddles and
 // order of operations of the five-pass kernels, so results are bitwise
 // theirs.  These sizes are bound by launches (three empty ones in a row take
-// 7.5 us) and by the chain of latencies inside each kernel; solves went from
-// five launches to, FP64 us per solve, 15.0 (from 20.7) at n = 16 and 32,
-// 21.0 (24.8) at n = 48, 22.6 (26.9) at n = 64, 47.8 (51.4) at n = 96, 76.4
-// (89.4) at n = 128; FP32
-// 18.8 (23.5) at n = 64, 50.0 (56.0) at n = 128.  Large ones are bound by F2
-// (39 of 72 us at n = 128), whose exchanges go through LDS; k_f_midw, which
-// does two of six in registers, took it from 59 us.
+// 7.5 us) and by the chain of latencies inside each kernel (times of both
+// routes at every length beside fused_length).  Large ones are bound by F2
+// (39 of 72 us at n = 128 FP64), whose exchanges go through LDS; k_f_midw,
+// which does two of six in registers, took it from 59 us.
 //
 // A holds R (n + 1) blocks [r][k3] of n rows i1 of M columns j (block pitch
 // FusedGeo::BLK): F2 reads and writes whole blocks, F1 and F3 touch J
@@ -83,15 +80,16 @@ template <typename T, int N> struct FusedCfg {
     static constexpr int J = N == 36 ? 2 : N == 108 ? 6 : N == 144 ? 12 : N == 256 ? 8 : N == 192 ? (sizeof(T) == 8 ? 12 : 8) : 4;
     static constexpr int KU = N == 144 || N == 256 ? 1 : N == 192 ? 2 : 3;
     // J of F1 and of F3, KU of F3, with several solves per launch: there are
-    // workgroups enough for wider rows of A (n = 64 7.34 -> 7.16 us per solve,
-    // FP32 4.69 -> 4.38; n = 128 FP32 40.1 -> 37.9; n = 72 15.7 -> 15.0)
+    // workgroups enough for wider rows of A (us per solve of a batch against
+    // the tiles of one solve, when chosen: n = 64 7.34 -> 7.16, FP32 4.69 ->
+    // 4.38; n = 128 FP32 40.1 -> 37.9; n = 72, which has only these, 15.7 -> 15.0)
     static constexpr int J1M = N == 128 ? 8 : N == 256 && sizeof(T) == 4 ? 16 : J;
     static constexpr int J3M = N == 128 ? 8 : N == 192 && sizeof(T) == 8 ? 4 : J;
     static constexpr int KUM = N == 128 ? 2 : N == 192 && sizeof(T) == 8 ? 3 : KU;
     static constexpr int NB = N <= 32 ? 4 : N == 36 ? 2 : 1;
     // the 17 MB of A of one solve at n = 64 FP64 written and read past the
-    // caches: 26.7 -> 24.2 us for the three launches (other sizes and several
-    // solves in one launch lose by it, n = 128 74 -> 84 us)
+    // caches: three launches 2.5 us faster (26.7 -> 24.2 when chosen; other
+    // sizes and several solves in one launch lose by it, n = 128 74 -> 84 us)
     static constexpr bool NT = N == 128 && sizeof(T) == 8;
     // whether the plans fit k_f_midw
     static constexpr bool W = N == 128 || N == 192 || N == 256;

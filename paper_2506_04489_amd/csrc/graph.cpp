@@ -1,8 +1,8 @@
 // graph.cpp - recorded solves and batches.  A record owns its workspaces and
 // (for batches) its device job table, written at capture, so its replays read
 // nothing from library state that later calls may change.  A batch is a HIP
-// graph.  A single solve keeps its launch arguments and replays as its three
-// or five kernel launches: hipGraphLaunch of such a chain took 20 us of host
+// graph.  A single solve keeps its launch arguments and replays as its one,
+// three or five kernel launches: hipGraphLaunch of such a chain took 20 us of host
 // time, the launches 2.5 us each (n = 48 FP32: 25.2 -> 16.8 us per
 // replay).
 #include <algorithm>

@@ -54,7 +54,7 @@ hipError_t launch_tables(const std::vector<TabJob> &jobs, const std::vector<TabT
 // ---- device resources ------------------------------------------------------
 struct DevSpectrum {            // the multiplier octant, shared between plans
     int device = -1;
-    double *mult = nullptr;     // blocked layout, (n+1)*P*(n+1) doubles
+    double *mult = nullptr;     // (n+1)*P*(n+1) doubles, laid out as MultAt says
     size_t bytes = 0;
     ~DevSpectrum();
 };

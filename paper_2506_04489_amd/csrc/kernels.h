@@ -100,15 +100,24 @@ constexpr bool plan_exists(int N, int pv) {
 // built for, and the radix plan of each axis it runs (0: i3, 1: i2, 2: i1).
 // A solve takes it when its shape has these plans, so that its result is
 // bitwise that of the five passes, and does not ask for the five passes'
-// tiles (Shape::five).  The lengths are those where three
-// launches measured faster, alone and several per launch, us per solve of
-// FP64 against five passes: n = 64 22.6 and 9.0 (26.9 and 13), n = 96 47.8
-// and 37.6 (51.4 and 41.6), n = 128 76.4 and 64 (89.4 and 91).  n = 72 only
-// with several solves per launch (14.3 against 17.7): one alone takes 37.1
-// against 34.0, as F2's 584 workgroups of nine waves leave the CUs one or two
-// each and its phases do not overlap.  For the same reason n = 96 in FP32
-// (20.1 against 24.9 for several, one alone 39.1 against 36.3).  n = 108 has
-// an F2 of 46 us against 26 for H3.
+// tiles (Shape::five).  Whole solves through the library, us, three launches
+// (one at n <= 8) against five passes of the same plans, one solve at a time
+// and per solve of a replayed batch of 12:
+//     n   FP64 one      FP64 of 12    FP32 one      FP32 of 12
+//     8    7.0 /  13.8   1.1 /  1.6    5.9 /  15.3   1.1 /  1.6
+//    16   12.7 /  15.4   1.6 /  1.9   12.3 /  15.6   1.5 /  1.8
+//    32   13.4 /  16.8   2.9 /  3.1   11.9 /  15.5   2.1 /  2.8
+//    48   20.7 /  24.5   6.0 /  7.0   16.6 /  20.1   4.2 /  4.7
+//    54   24.8 /  25.4   8.4 /  7.9   17.8 /  20.1   5.0 /  5.6
+//    64   21.9 /  28.2   7.8 / 12.3   18.1 /  23.2   5.0 /  8.2
+//    72      - /  33.9  15.5 / 16.3      - /  25.9   8.5 / 10.8
+//    96   47.4 /  54.1  34.5 / 43.4      - /  36.2  17.7 / 23.8
+//   128   74.1 /  87.4  66.5 /  100   50.5 /  56.4  38.8 / 52.7
+// (FP64 five passes with other plans take 30.8 at n = 64, 50.4 at 96 and 88.0
+// at 128).  One solve alone stays on five passes at n = 72 (three launches
+// 37.1), as F2's 584 workgroups of nine waves leave the CUs one or two each
+// and its phases do not overlap, and for the same reason at n = 96 in FP32
+// (39.1).  n = 108 has an F2 of 46 us against 26 for H3.
 constexpr bool fused_length(int N) {
     return N == 8 || N == 12 || N == 16 || N == 24 || N == 32 || N == 36 || N == 48 || N == 64 || N == 72 ||
            N == 96 || N == 108 || N == 128 || N == 144 || N == 192 || N == 256;
@@ -134,7 +143,13 @@ inline Shape route_pick(int N, Shape five, float five_ms, Shape three, float thr
 // Layout of a multiplier octant: element (|k1| = a, |k2| = b, k3 = c) of the
 // (n2+1) x P x (n1+1) doubles.  Rows ([b][c][a], for cubes of a fused
 // length): the fused pass reads all a of one (b, c).  Blocked
-// ([b][c/8][a][c%8], the others): the i1 pass reads 8 c of each a.
+// ([b][c/8][a][c%8], the others): the i1 pass reads 8 c of each a.  Cubes of
+// a fused length that run five passes read rows there too; that costs H3
+// (rows against blocked, us) in FP64 nothing at n = 72 (10.7) and 1% at 96
+// and 128, in FP32 8.8 against 8.4 at n = 72, 13.6 against 12.9 at 96 and 22.4
+// against 21.4 at 128: 2% of one FP32 solve of n = 72 or 96, the only
+// unprofiled ones concerned.  Plans of both tiers share an octant, and their
+// batches gain more by the three launches.
 struct MultAt {
     bool rows;
     int P, na;      // pitch of c, n1 + 1
@@ -161,7 +176,7 @@ struct PJob {
     void *u;
     void *X;                 // n*n*P complex
     void *A;                 // n planes of `plane` complex, rows of pa
-    const double *mult;      // blocked multiplier octant
+    const double *mult;      // multiplier octant (MultAt)
     const void *tw64;       // twiddles double2[N], both tiers
     int N;                   // padded length
     int P;                   // k3 pitch of X
@@ -209,7 +224,7 @@ struct SolveArgs {
     Shape shape;         // launch shape (ignored by the uncropped variant)
     void *A2 = nullptr;  // N*N*P complex, full variant only
     void *Y2 = nullptr;  // N*N*P complex, full variant only
-    const double *mult = nullptr;   // blocked multiplier octant
+    const double *mult = nullptr;   // multiplier octant (MultAt)
     const void *tw64 = nullptr;    // twiddles double2[N], both tiers
     hipEvent_t *ev = nullptr;       // optional profiling events, one before each launch and one after
     int *ev_pass = nullptr;         // host array: pass (0..4) of each launch, -1 for the last event

@@ -395,11 +395,12 @@ def solve_batched(plans: Sequence[Plan], rhos, us, stream=None):
 
 
 class Graph:
-    """A solve (or batch) captured as a HIP graph: psp_graph_*."""
+    """A recorded solve (replayed as its kernel launches) or batch (a HIP
+    graph): psp_graph_*."""
 
     def __init__(self, handle, keep):
         self._h = handle
-        self._keep = keep            # tensors and plans the graph points into
+        self._keep = keep            # tensors and plans the record points into
 
     @classmethod
     def capture(cls, plan: "Plan", rho, u, stream=None):
