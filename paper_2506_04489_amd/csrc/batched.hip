@@ -67,6 +67,13 @@ static void image_layout(const std::vector<BatchMember> &m, BatchImage *img) {
     img->bytes = align256(img->group_off + img->grouped.size() * sizeof(Job));
 }
 
+// one past the last grouped member with the size and shape of the i-th
+static size_t group_end(const std::vector<BatchMember> &m, const std::vector<int> &g, size_t i) {
+    size_t j = i;
+    while (j < g.size() && m[g[j]].n == m[g[i]].n && m[g[j]].shape == m[g[i]].shape) ++j;
+    return j;
+}
+
 // items of pass p for one solve on the persistent path
 static int persist_items(int n, int pv, int p) {
     const int N = 2 * n, tpc = persist_tpc(N, pv);
@@ -126,6 +133,22 @@ void build_batch_image(const std::vector<BatchMember> &m, bool f32, unsigned cha
     std::memcpy(host.data() + img->hdr_off, &hdr, sizeof(hdr));
     Job *gt = (Job *)(host.data() + img->group_off);
     for (size_t i = 0; i < img->grouped.size(); ++i) gt[i] = m[img->grouped[i]].job;
+    // groups that one workgroup per solve must not run (here and not at the
+    // launch, which may be under stream capture and so does not allocate)
+    const std::vector<int> &g = img->grouped;
+    img->five.assign(g.size(), 0);
+    for (size_t i = 0, j; i < g.size(); i = j) {
+        j = group_end(m, g, i);
+        const int n = m[g[i]].n;
+        if (2 * n > SINGLE_MAX || j - i < 2) continue;
+        std::vector<const void *> rho;
+        std::vector<void *> u;
+        for (size_t q = i; q < j; ++q) {
+            rho.push_back(m[g[q]].job.rho);
+            u.push_back(m[g[q]].job.u);
+        }
+        if (feeds_another(rho, u, (size_t)n * n * n * (f32 ? 4 : 8))) img->five[i] = 1;
+    }
 }
 
 hipError_t launch_batch_image(const std::vector<BatchMember> &m, const BatchImage &img, bool f32,
@@ -138,19 +161,10 @@ hipError_t launch_batch_image(const std::vector<BatchMember> &m, const BatchImag
     const std::vector<int> &g = img.grouped;
     size_t i = 0;
     while (i < g.size()) {
-        size_t j = i;
+        const size_t j = group_end(m, g, i);
         const BatchMember &b = m[g[i]];
-        while (j < g.size() && m[g[j]].n == b.n && m[g[j]].shape == b.shape) ++j;
         Shape shape = b.shape;
-        if (2 * b.n <= SINGLE_MAX && j - i > 1) {
-            std::vector<const void *> rho;
-            std::vector<void *> u;
-            for (size_t k = i; k < j; ++k) {
-                rho.push_back(m[g[k]].job.rho);
-                u.push_back(m[g[k]].job.u);
-            }
-            if (feeds_another(rho, u, (size_t)b.n * b.n * b.n * (f32 ? 4 : 8))) shape.five = true;
-        }
+        if (img.five[i]) shape.five = true;
         hipError_t e = launch_group(b.n, f32, shape, (const Job *)(dev_base + img.group_off) + i, (int)(j - i),
                                     b.tw64, st);
         if (e != hipSuccess) return e;

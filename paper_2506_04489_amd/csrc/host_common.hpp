@@ -123,6 +123,7 @@ struct BatchMember {
 struct BatchImage {
     std::vector<int> persist;     // members on the persistent path (2n <= PB_MAX_N), in table order
     std::vector<int> grouped;     // the others, sorted by (n, shape)
+    std::vector<char> five;       // of the first member of a group: the group takes five passes
     size_t hdr_off = 0, jobs_off = 0, start_off = 0, group_off = 0, bytes = 0;
     int total[kPasses] = {0, 0, 0, 0, 0};
     bool flat = false;            // one workgroup per item instead of persistent workgroups

@@ -233,3 +233,25 @@ def test_persistent_kernels_at_every_length_and_plan(mode, dtype):
         torch.cuda.synchronize()
         assert p.profile_read()[0] == 1
         assert torch.equal(u, five), (n, plan)
+
+
+def test_recorded_batch_with_outputs_over_other_members_inputs():
+    """The same through a recorded batch: a replay solves every input as it was
+    when the replay began."""
+    import torch
+    n, k = 8, 6
+    p = B.Plan(n, 2.0 / n, 40).precompute()
+    g = torch.Generator().manual_seed(9)
+    buf = torch.randn((k, n, n, n), generator=g, dtype=torch.float64).cuda()
+    rhos, us = [buf[i] for i in range(k)], [buf[(i + 1) % k] for i in range(k)]
+    rec = B.Graph.capture_batched([p] * k, rhos, us)
+    for _ in range(3):
+        want = [p.solve(r.clone()) for r in rhos]
+        torch.cuda.synchronize()
+        rec.launch()
+        torch.cuda.synchronize()
+        for u, w in zip(us, want):
+            assert torch.equal(u, w)
+        buf.add_(0.25)                      # eager work between the replays
+        torch.cuda.synchronize()
+    rec.close()
